@@ -97,6 +97,15 @@ struct KernelTimer {
 };
 KernelTimer*& kernel_timer();
 
+// A value that has been loaded, whatever becomes of it: without this the
+// compiler sinks a load into the select that may drop it, which makes a chain
+// of branches with a wait each out of loads that could all be in flight.
+__device__ inline void pin(double& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(v));
+#endif
+}
+
 // ---------------------------------------------------------------------------
 // Wave reductions on the DPP / permlane paths (register-to-register lane
 // moves, no LDS round trip).  Every lane of a group ends with the group's sum,
@@ -193,8 +202,9 @@ void copy_f64(hipStream_t s, const double* X, int64_t ldx, double* Y, int64_t ld
 // Y = alpha * X^T (X rows x cols -> Y cols x rows)
 void transpose_f64(hipStream_t s, const double* X, int64_t ldx, double* Y, int64_t ldy,
                    int64_t rows, int64_t cols, double alpha);
-// Y = a*X1 + b*X2 + c*X3 + d*I   (any of X1..X3 may be null when its coefficient is 0)
-void lincomb3_f64(hipStream_t s, int64_t n, double a, const double* X1, double b,
+// Y = a*X1 + b*X2 + c*X3 + d*I, n x n at leading dimension ld, the padding rows
+// with them (any of X1..X3 may be null when its coefficient is 0)
+void lincomb3_f64(hipStream_t s, int64_t n, int64_t ld, double a, const double* X1, double b,
                   const double* X2, double c, const double* X3, double d, double* Y);
 // X *= alpha (n x n, contiguous)
 void scale_f64(hipStream_t s, double* X, int64_t count, double alpha);
@@ -220,13 +230,12 @@ void finite_check_f64(hipStream_t s, const double* X, int64_t rows, int64_t cols
 
 // LU with partial pivoting and the Pade solve (lu.hip)
 struct LuWork;
-// Solve P X = Q in place (Q <- P^-1 Q); P is destroyed.  n x n contiguous.
-// Returns through *info_dev (device int): 0 ok, j+1 if pivot j is exactly zero.
-void lu_solve_f64(hipStream_t s, int64_t n, double* P, double* Q, Arena& ws, int* info_dev);
-size_t lu_solve_workspace(int64_t n);
-// The same with an n x nrhs right-hand side Q (ld ldq).
-void lu_solve_f64(hipStream_t s, int64_t n, double* P, double* Q, int64_t ldq, int64_t nrhs, Arena& ws,
+// Solve P X = Q in place (Q <- P^-1 Q); P (n x n, ld ldp) is destroyed, Q is
+// n x nrhs (ld ldq).  Returns through *info_dev (device int): 0 ok, j+1 if pivot
+// j is exactly zero.
+void lu_solve_f64(hipStream_t s, int64_t n, double* P, int64_t ldp, double* Q, int64_t ldq, int64_t nrhs, Arena& ws,
                   int* info_dev);
+size_t lu_solve_workspace(int64_t n);
 size_t lu_solve_workspace(int64_t n, int64_t nrhs);
 
 // A second stream beside the caller's, a ring of events for the waits

@@ -47,15 +47,15 @@ __global__ void transpose_kernel(const double* X, int64_t ldx, double* Y, int64_
   }
 }
 
-__global__ void lincomb3_kernel(int64_t n, double a, const double* X1, double b, const double* X2,
+__global__ void lincomb3_kernel(int64_t n, int64_t ld, double a, const double* X1, double b, const double* X2,
                                 double c, const double* X3, double d, double* Y) {
-  const int64_t total = n * n;
+  const int64_t total = ld * n;
   for (int64_t i = blockIdx.x * (int64_t)kT + threadIdx.x; i < total; i += (int64_t)gridDim.x * kT) {
     double v = 0.0;
     if (X1) v += a * X1[i];
     if (X2) v += b * X2[i];
     if (X3) v += c * X3[i];
-    if ((i % n) == (i / n)) v += d;
+    if ((i % ld) == (i / ld)) v += d;
     Y[i] = v;
   }
 }
@@ -200,10 +200,10 @@ void transpose_f64(hipStream_t s, const double* X, int64_t ldx, double* Y, int64
   DME_HIP(hipGetLastError());
 }
 
-void lincomb3_f64(hipStream_t s, int64_t n, double a, const double* X1, double b, const double* X2,
+void lincomb3_f64(hipStream_t s, int64_t n, int64_t ld, double a, const double* X1, double b, const double* X2,
                   double c, const double* X3, double d, double* Y) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(lincomb3_kernel, dim3(grid_for(n * n)), dim3(kT), 0, s, n, a, X1, b, X2, c,
+  hipLaunchKernelGGL(lincomb3_kernel, dim3(grid_for(ld * n)), dim3(kT), 0, s, n, ld, a, X1, b, X2, c,
                      X3, d, Y);
   DME_HIP(hipGetLastError());
 }

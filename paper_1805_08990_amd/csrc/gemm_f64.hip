@@ -6,12 +6,11 @@
 // tall-skinny products of the Householder compression (split-K).
 //
 // Tile structure: a 256-thread workgroup (4 wave64s as 2 x 2) owns a BM x BN
-// block of C; op(A) and op(B) slabs of depth BK are staged through LDS with
-// the next slab prefetched into registers while the current one feeds
-// v_mfma_f64_16x16x4_f64.  The MFMA is fed with op(B) as its first operand
-// and op(A) as its second so that the accumulator lanes hold 16 consecutive
-// rows of C: the epilogue stores are then contiguous 128-byte runs of a C
-// column.  Split-K writes partial tiles to a workspace and a second kernel
+// block of C; op(A) and op(B) slabs of depth kBK go to LDS directly, the next
+// one while the current one feeds v_mfma_f64_16x16x4_f64.  The MFMA is fed with
+// op(B) as its first operand and op(A) as its second so that the accumulator
+// lanes hold 16 rows of C each: the epilogue stores are then contiguous runs of
+// a C column.  Split-K writes partial tiles to a workspace and a second kernel
 // adds them in fixed order, so results are deterministic.
 #include "common.h"
 
@@ -21,30 +20,174 @@ namespace {
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
-constexpr int kPad = 16;  // LDS row padding in doubles (staggers the 4 k-rows of a fragment read)
 
-template <int BM, int BN, int BK, bool TA, bool TB>
-__global__ __launch_bounds__(kThreads) void gemm_f64_kernel(
+// Loads on their way to LDS have arrived, of every wave.
+__device__ inline void arrive() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+#endif
+  __syncthreads();
+}
+
+constexpr int kBK = 16;  // depth of a slab
+
+// One operand's slab (B rows or columns of C, kBK deep) on its way to LDS.
+// KC: the operand is contiguous along k (op(A) = A^T, op(B) = B); its slab is
+// stored [B][kBK] with the eight 16-byte pieces of a row rotated by
+// (row / 2) % 8, so that 16 lanes reading the same piece of 16 rows hit every
+// bank once.  !KC: contiguous along the B direction, stored [kBK][B].
+// Whole slabs go straight to LDS, 16 bytes a lane where the operand allows
+// (VEC: base, leading dimension and extent even), else 4 bytes a lane; rows
+// past the extent repeat the last one (their products are not stored).  The
+// last slab, if it is not whole, goes through registers with zeros behind kend.
+template <bool KC, int B, bool VEC>
+struct Slab {
+  static constexpr int kVecInstr = B / 32;  // 16-byte loads of a wave per slab
+  const double* base;                       // at (row0, 0)
+  int64_t ld;
+  int rows;                                 // extent past row0
+  const double* p[VEC ? kVecInstr : 1];
+
+  __device__ void init(const double* X, int64_t ldx, int row0, int extent, int kbeg, int wave, int lane) {
+    base = KC ? X + (int64_t)row0 * ldx : X + row0;
+    ld = ldx;
+    rows = extent - row0;
+    if (VEC) {
+#pragma unroll
+      for (int u = 0; u < kVecInstr; ++u) {
+        const int q = (wave + 4 * u) * 64 + lane;
+        if (KC) {
+          const int r = q / (kBK / 2), c = (q % (kBK / 2)) ^ ((r >> 1) & 7);
+          p[u] = base + (int64_t)min(r, rows - 1) * ld + kbeg + 2 * c;
+        } else {
+          const int k = q / (B / 2), r = 2 * (q % (B / 2));
+          p[u] = base + min(r, ((rows + 1) & ~1) - 2) + (int64_t)(kbeg + k) * ld;
+        }
+      }
+    }
+  }
+  __device__ void to_lds(double* s, int k0, int wave, int lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef const __attribute__((address_space(1))) void* gp;
+    typedef __attribute__((address_space(3))) void* lp;
+    if (VEC) {
+#pragma unroll
+      for (int u = 0; u < kVecInstr; ++u) {
+        __builtin_amdgcn_global_load_lds((gp)p[u], (lp)(s + (wave + 4 * u) * 128), 16, 0, 0);
+        p[u] += KC ? (int64_t)kBK : (int64_t)kBK * ld;
+      }
+    } else {
+const int hi = lane >> 5, w = (lane >> 1) & (kBK - 1);
+      // a lane takes half of double 32 ii + lane / 2, ii = wave + 4 u
+      if (KC) {
+        if (rows >= B) {
+          const double* q = base + (int64_t)(2 * wave + hi) * ld + k0 + (w & 1);
+          const int c0 = 2 * ((w >> 1) ^ (wave & 7)), c1 = 2 * ((w >> 1) ^ ((wave + 4) & 7));
+#pragma unroll 4
+          for (int u = 0; u < 4 * kVecInstr; ++u) {
+            const int* src = reinterpret_cast<const int*>(q + ((u & 1) ? c1 : c0)) + (lane & 1);
+            __builtin_amdgcn_global_load_lds((gp)src, (lp)(s + (wave + 4 * u) * 32), 4, 0, 0);
+            q += 8 * ld;
+          }
+        } else {
+#pragma unroll 1
+          for (int u = 0; u < 4 * kVecInstr; ++u) {
+            const int ii = wave + 4 * u, r = 2 * ii + hi, c = (w >> 1) ^ (ii & 7);
+            const double* q = base + (int64_t)min(r, rows - 1) * ld + k0 + 2 * c + (w & 1);
+            __builtin_amdgcn_global_load_lds((gp)(reinterpret_cast<const int*>(q) + (lane & 1)), (lp)(s + ii * 32), 4, 0, 0);
+          }
+        }
+      } else {
+        constexpr int PER = B / 32;  // loads of a k row
+        const int r = (wave % PER) * 32 + (lane >> 1);
+        const double* q = base + min(r, rows - 1) + (int64_t)(k0 + wave / PER) * ld;
+#pragma unroll 4
+        for (int u = 0; u < 4 * kVecInstr; ++u) {
+          __builtin_amdgcn_global_load_lds((gp)(reinterpret_cast<const int*>(q) + (lane & 1)), (lp)(s + (wave + 4 * u) * 32), 4, 0, 0);
+          q += (4 / PER) * ld;
+        }
+      }
+    }
+#endif
+  }
+  __device__ void tail_to_lds(double* s, int k0, int kend, int tid) {
+    constexpr int NE = B * kBK / kThreads;
+    double v[NE];
+#pragma unroll
+    for (int u = 0; u < NE; ++u) {
+      const int d = tid + u * kThreads;
+      int r, k;
+      if (KC) { r = d / kBK; k = (((d % kBK) >> 1) ^ ((r >> 1) & 7)) * 2 + (d & 1); }
+      else    { k = d / B; r = d % B; }
+      const int kk = min(k0 + k, kend - 1), rr = min(r, rows - 1);
+      v[u] = KC ? base[(int64_t)rr * ld + kk] : base[rr + (int64_t)kk * ld];
+    }
+#pragma unroll
+    for (int u = 0; u < NE; ++u) pin(v[u]);
+#pragma unroll
+    for (int u = 0; u < NE; ++u) {
+      const int d = tid + u * kThreads;
+      const int k = KC ? (((d % kBK) >> 1) ^ (((d / kBK) >> 1) & 7)) * 2 + (d & 1) : d / B;
+      s[d] = k0 + k < kend ? v[u] : 0.0;
+    }
+  }
+  // fragments of T 16-row tiles from row w0 on, k = 8 h + 2 kq and + 1.  A tile
+  // is 16 consecutive rows (KC) or every other row of 32 (!KC).
+  template <int T>
+  static __device__ void frags(const double* s, int w0, int h, int r16, int kq, double (&f)[T][2]) {
+    typedef double v2d __attribute__((ext_vector_type(2)));
+    if (KC) {
+#pragma unroll
+      for (int i = 0; i < T; ++i) {
+        const int r = w0 + 16 * i + r16, c = (4 * h + kq) ^ ((r16 >> 1) & 7);
+        const v2d v = *reinterpret_cast<const v2d*>(s + r * kBK + 2 * c);
+        f[i][0] = v.x;
+        f[i][1] = v.y;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int i = 0; i < T; i += 2) {
+          const v2d v = *reinterpret_cast<const v2d*>(s + (8 * h + 2 * kq + e) * B + w0 + 16 * i + 2 * r16);
+          f[i][e] = v.x;
+          f[i + 1][e] = v.y;
+        }
+    }
+  }
+  // row of C of a tile's row r
+  static __device__ int row(int tile, int r) { return KC ? 16 * tile + r : 16 * (tile & ~1) + 2 * r + (tile & 1); }
+};
+
+// A workgroup of four waves (2 x 2) owns a BM x BN block of C.  FP64 MFMA takes
+// 64 cycles for a 16 x 16 x 4 step, so a wave's 64 x 64 block is 4096 cycles of
+// MFMA per slab and the kernel is bound by it as long as nothing else stops the
+// waves: the slabs go to LDS without registers or guards between, into two
+// buffers with one barrier a slab, and a lane takes two k or two rows per LDS
+// read.  Random operands, n x n x n: 66 TFLOP/s at 4096 and 70 at 8192 (50 and 51
+// with the slabs through registers behind bounds checks and two barriers a
+// slab); 4032 x 8128 x 64 added to C, bound by C's traffic, 132 us (240).
+template <int BM, int BN, bool TA, bool TB, bool VEC>
+__global__ __launch_bounds__(kThreads, 2) void gemm_f64_kernel(
     int M, int N, int K, int kchunk, double alpha, const double* __restrict__ A, int64_t lda,
     const double* __restrict__ B, int64_t ldb, double beta, double* __restrict__ C, int64_t ldc,
     double* __restrict__ partial) {
   constexpr int WTM = BM / 2, WTN = BN / 2;  // wave tile
   constexpr int TM = WTM / 16, TN = WTN / 16;
-  constexpr int LA = BM * BK / kThreads;  // A elements per thread per slab
-  constexpr int LB = BN * BK / kThreads;
-  static_assert(LA * kThreads == BM * BK && LB * kThreads == BN * BK, "tile/thread mismatch");
-
-  __shared__ double sA[BK][BM + kPad];
-  __shared__ double sB[BK][BN + kPad];
+  typedef Slab<TA, BM, VEC> SA;
+  typedef Slab<!TB, BN, VEC> SB;
+  __shared__ alignas(16) double sh[2][(BM + BN) * kBK];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave & 1, wn = wave >> 1;
   const int m0 = blockIdx.x * BM;
   const int n0 = blockIdx.y * BN;
   const int kbeg = blockIdx.z * kchunk;
   const int kend = min(K, kbeg + kchunk);
+  const int r16 = lane & 15;
+  const int kq = lane >> 4;
 
   v4d acc[TM][TN];
 #pragma unroll
@@ -52,94 +195,103 @@ __global__ __launch_bounds__(kThreads) void gemm_f64_kernel(
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
 
-  double ra[LA], rb[LB];
-
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < LA; ++i) {
-      const int idx = tid + i * kThreads;
-      int ml, kl;
-      if (!TA) { ml = idx % BM; kl = idx / BM; }
-      else     { kl = idx % BK; ml = idx / BK; }
-      const int m = m0 + ml, k = k0 + kl;
-      double v = 0.0;
-      if (m < M && k < kend) v = TA ? A[k + (int64_t)m * lda] : A[m + (int64_t)k * lda];
-      ra[i] = v;
-    }
-#pragma unroll
-    for (int i = 0; i < LB; ++i) {
-      const int idx = tid + i * kThreads;
-      int nl, kl;
-      if (!TB) { kl = idx % BK; nl = idx / BK; }
-      else     { nl = idx % BN; kl = idx / BN; }
-      const int n = n0 + nl, k = k0 + kl;
-      double v = 0.0;
-      if (n < N && k < kend) v = TB ? B[n + (int64_t)k * ldb] : B[k + (int64_t)n * ldb];
-      rb[i] = v;
+  SA a;
+  SB b;
+  a.init(A, lda, m0, M, kbeg, wave, lane);
+  b.init(B, ldb, n0, N, kbeg, wave, lane);
+  // (an odd extent reads a padding row with its last one; behind the matrix's
+  // last column there need be none, so that column never goes the direct way)
+  const bool odd = (!TA && (M & 1)) || (TB && (N & 1));
+  const int kwhole = kend - (VEC && odd && kend == K ? 1 : 0);
+  auto fetch = [&](double* s, int k0) {
+    if (k0 + kBK <= kwhole) {
+      a.to_lds(s, k0, wave, lane);
+      b.to_lds(s + BM * kBK, k0, wave, lane);
+    } else if (k0 < kend) {
+      a.tail_to_lds(s, k0, kend, tid);
+      b.tail_to_lds(s + BM * kBK, k0, kend, tid);
     }
   };
-  auto store = [&]() {
+  auto multiply = [&](const double* s) {
 #pragma unroll
-    for (int i = 0; i < LA; ++i) {
-      const int idx = tid + i * kThreads;
-      int ml, kl;
-      if (!TA) { ml = idx % BM; kl = idx / BM; }
-      else     { kl = idx % BK; ml = idx / BK; }
-      sA[kl][ml] = ra[i];
-    }
+    for (int h = 0; h < kBK / 8; ++h) {
+      double fm[TM][2], fn[TN][2];
+      SB::template frags<TN>(s + BM * kBK, wn * WTN, h, r16, kq, fn);
+      SA::template frags<TM>(s, wm * WTM, h, r16, kq, fm);
 #pragma unroll
-    for (int i = 0; i < LB; ++i) {
-      const int idx = tid + i * kThreads;
-      int nl, kl;
-      if (!TB) { kl = idx % BK; nl = idx / BK; }
-      else     { nl = idx % BN; kl = idx / BN; }
-      sB[kl][nl] = rb[i];
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fn[j][e], fm[i][e], acc[i][j], 0, 0, 0);
     }
   };
-
-  const int r16 = lane & 15;
-  const int kq = lane >> 4;
-
-  if (kbeg < kend) load(kbeg);
-  for (int k0 = kbeg; k0 < kend; k0 += BK) {
-    __syncthreads();
-    store();
-    __syncthreads();
-    if (k0 + BK < kend) load(k0 + BK);
-#pragma unroll
-    for (int kk = 0; kk < BK / 4; ++kk) {
-      double fa[TN], fb[TM];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) fa[j] = sB[kk * 4 + kq][wn * WTN + j * 16 + r16];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) fb[i] = sA[kk * 4 + kq][wm * WTM + i * 16 + r16];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[j], fb[i], acc[i][j], 0, 0, 0);
-    }
+  int cur = 1;
+#pragma unroll 1
+  for (int k0 = kbeg - kBK; k0 < kend; k0 += kBK) {
+    arrive();
+    fetch(sh[cur ^ 1], k0 + kBK);
+    if (k0 >= kbeg) multiply(sh[cur]);
+    cur ^= 1;
   }
 
   // Epilogue.  The FP64 16x16x4 MFMA leaves element v of lane l at row
   // 4 v + l / 16, column l % 16 of its 16 x 16 result (rows of the result are
-  // columns of C here): lane holds C(m = base_m + r16, n = base_n + 4*v + kq).
+  // columns of C here).
+  // A lane's rows come in pairs of neighbours (!TA): 16-byte accesses where C
+  // allows.  The old entries of a column group are read while the group before
+  // is written (a short K is bound by C's traffic).
+  typedef double v2d __attribute__((ext_vector_type(2)));
+  const bool scaled = !partial;
+  const bool read = scaled && beta != 0.0;
+  double* const Cb = partial ? partial + (int64_t)blockIdx.z * M * N : C;
+  const int64_t ldo = partial ? M : ldc;
+  const int mw = m0 + wm * WTM, nw = n0 + wn * WTN;
+  const bool pairs = !TA && ldo % 2 == 0 && reinterpret_cast<uintptr_t>(Cb) % 16 == 0 && mw + WTM <= M;
+  double old[2][4][TM];
+  auto read_old = [&](int j, double (&o)[4][TM]) {
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int m = m0 + wm * WTM + i * 16 + r16;
+    for (int v = 0; v < 4; ++v) {
+      const double* c = Cb + (int64_t)min(nw + SB::row(j, 4 * v + kq), N - 1) * ldo;
+      if (pairs) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
+        for (int i = 0; i < TM; i += 2) {
+          const v2d x = *reinterpret_cast<const v2d*>(c + mw + SA::row(i, r16));
+          o[v][i] = x.x;
+          o[v][i + 1] = x.y;
+        }
+      } else {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int n = n0 + wn * WTN + j * 16 + v * 4 + kq;
-        if (m < M && n < N) {
-          if (partial) {
-            partial[(int64_t)blockIdx.z * M * N + m + (int64_t)n * M] = acc[i][j][v];
-          } else {
-            double* c = C + m + (int64_t)n * ldc;
-            const double out = alpha * acc[i][j][v];
-            *c = (beta == 0.0) ? out : out + beta * (*c);
-          }
+        for (int i = 0; i < TM; ++i) o[v][i] = c[min(mw + SA::row(i, r16), M - 1)];
+      }
+    }
+  };
+  if (read) read_old(0, old[0]);
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    if (read && j + 1 < TN) read_old(j + 1, old[(j + 1) & 1]);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int n = nw + SB::row(j, 4 * v + kq);
+      double* c = Cb + (int64_t)n * ldo;
+      double out[TM];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        out[i] = acc[i][j][v];
+        if (scaled) out[i] *= alpha;
+        if (read) out[i] += beta * old[j & 1][v][i];
+      }
+      if (n >= N) continue;
+      if (pairs) {
+#pragma unroll
+        for (int i = 0; i < TM; i += 2)
+          *reinterpret_cast<v2d*>(c + mw + SA::row(i, r16)) = v2d{out[i], out[i + 1]};
+      } else {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          const int m = mw + SA::row(i, r16);
+          if (m < M) c[m] = out[i];
         }
       }
     }
@@ -384,29 +536,38 @@ bool use_syrk(char ta, char tb, int64_t M, int64_t N, int64_t K, const double* A
          M <= 16 * kSyMaxT && K >= kSyMinK;
 }
 
-template <int BM, int BN, int BK, bool TA, bool TB>
+// 16-byte loads of an operand's slabs: base and leading dimension even; where
+// the contiguous direction is the one cut by tiles its extent too, or padded
+// (whole slabs start at even k).
+bool vec_ok(const double* X, int64_t ld, bool kc, int64_t extent) {
+  return reinterpret_cast<uintptr_t>(X) % 16 == 0 && ld % 2 == 0 && (kc || extent % 2 == 0 || ld > extent);
+}
+
+template <int BM, int BN, bool TA, bool TB>
 void launch_tile(hipStream_t s, int M, int N, int K, int nsplit, int kchunk, double alpha,
                  const double* A, int64_t lda, const double* B, int64_t ldb, double beta,
                  double* C, int64_t ldc, double* partial) {
   dim3 grid((unsigned)cdiv(M, BM), (unsigned)cdiv(N, BN), (unsigned)nsplit);
-  hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, BK, TA, TB>), grid, dim3(kThreads), 0, s, M, N, K,
-                     kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
+  // both operands in 16-byte pieces or both in 4-byte ones
+  auto kern = vec_ok(A, lda, TA, M) && vec_ok(B, ldb, !TB, N) ? gemm_f64_kernel<BM, BN, TA, TB, true>
+                                                              : gemm_f64_kernel<BM, BN, TA, TB, false>;
+  hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, M, N, K, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
 }
 
-template <int BM, int BN, int BK>
+template <int BM, int BN>
 void dispatch_trans(hipStream_t s, char ta, char tb, int M, int N, int K, int nsplit, int kchunk,
                     double alpha, const double* A, int64_t lda, const double* B, int64_t ldb,
                     double beta, double* C, int64_t ldc, double* partial) {
   const bool TA = (ta == 'T' || ta == 't');
   const bool TB = (tb == 'T' || tb == 't');
   if (!TA && !TB)
-    launch_tile<BM, BN, BK, false, false>(s, M, N, K, nsplit, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
+    launch_tile<BM, BN, false, false>(s, M, N, K, nsplit, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
   else if (TA && !TB)
-    launch_tile<BM, BN, BK, true, false>(s, M, N, K, nsplit, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
+    launch_tile<BM, BN, true, false>(s, M, N, K, nsplit, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
   else if (!TA && TB)
-    launch_tile<BM, BN, BK, false, true>(s, M, N, K, nsplit, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
+    launch_tile<BM, BN, false, true>(s, M, N, K, nsplit, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
   else
-    launch_tile<BM, BN, BK, true, true>(s, M, N, K, nsplit, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
+    launch_tile<BM, BN, true, true>(s, M, N, K, nsplit, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
 }
 
 // Skinny product Y = E X for a tall square operator E (M x K, M, K large)
@@ -609,7 +770,6 @@ struct Plan {
   int bm, bn, nsplit, kchunk;
 };
 
-constexpr int kBK = 16;
 constexpr int kTargetBlocks = 1024;  // ~4 workgroups per CU on 256 CUs
 constexpr int kMinKChunk = 256;
 constexpr int64_t kMinTiles = 256;      // one tile per CU
@@ -756,11 +916,11 @@ void gemm_f64(hipStream_t s, char ta, char tb, int64_t M, int64_t N, int64_t K, 
   }
   const int iM = (int)M, iN = (int)N, iK = (int)K;
   if (p.bm == 128 && p.bn == 128)
-    dispatch_trans<128, 128, kBK>(s, ta, tb, iM, iN, iK, p.nsplit, p.kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
+    dispatch_trans<128, 128>(s, ta, tb, iM, iN, iK, p.nsplit, p.kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
   else if (p.bm == 128)
-    dispatch_trans<128, 64, kBK>(s, ta, tb, iM, iN, iK, p.nsplit, p.kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
+    dispatch_trans<128, 64>(s, ta, tb, iM, iN, iK, p.nsplit, p.kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
   else
-    dispatch_trans<64, 64, kBK>(s, ta, tb, iM, iN, iK, p.nsplit, p.kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
+    dispatch_trans<64, 64>(s, ta, tb, iM, iN, iK, p.nsplit, p.kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
   DME_HIP(hipGetLastError());
   if (partial) {
     const int64_t total = M * N;

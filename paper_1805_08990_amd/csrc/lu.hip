@@ -42,15 +42,6 @@ struct Moves {
   int src[kPW];
 };
 
-// A value that has been loaded, whatever becomes of it: without this the
-// compiler sinks a load into the select that may drop it, which makes a chain
-// of branches with a wait each out of loads that could all be in flight.
-__device__ inline void pin(double& v) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("" : "+v"(v));
-#endif
-}
-
 // value of lane S of each aligned group of four
 template <int S>
 __device__ inline double quad_bcast_f64(double v) {
@@ -517,15 +508,10 @@ size_t lu_solve_workspace(int64_t n, int64_t nrhs) {
   return b;
 }
 
-void lu_solve_f64(hipStream_t s, int64_t n, double* A, double* Q, Arena& ws, int* info_dev) {
-  lu_solve_f64(s, n, A, Q, n, n, ws, info_dev);
-}
-
-void lu_solve_f64(hipStream_t s, int64_t n, double* A, double* Q, int64_t ldq, int64_t nrhs, Arena& ws,
+void lu_solve_f64(hipStream_t s, int64_t n, double* A, int64_t lda, double* Q, int64_t ldq, int64_t nrhs, Arena& ws,
                   int* info_dev) {
   if (n <= 0) return;
   DME_REQUIRE(n < (1ll << 30) && nrhs < (1ll << 30), DME_EINVAL, "LU: dimensions too large");
-  const int64_t lda = n;
   int* lists[2] = {ws.get<int>(lu_named(n)), ws.get<int>(lu_named(n))};
   Moves* mv = ws.get<Moves>(2);
   double* lbuf = ws.get<double>((size_t)kPW * kLeaf);
