@@ -182,6 +182,17 @@ void gemm_f64(hipStream_t s, char ta, char tb, int64_t M, int64_t N, int64_t K,
               double alpha, const double* A, int64_t lda, const double* B, int64_t ldb,
               double beta, double* C, int64_t ldc, Arena* ws = nullptr);
 
+// C = alpha A op(B) + beta C (n x n, inner dimension K) where the result is known
+// to be symmetric (products of commuting symmetric matrices, W P^T of a symmetric
+// update), at half the work: only C's lower triangle is computed, and written on
+// both sides (mirror; op(B) = B) or on its own (op(B) = B^T), then without rows
+// and columns [skip0, skip1).  Operands at even leading dimensions, 16-byte
+// aligned; an operand with an odd number of contiguous rows needs a padding row.
+void gemm_sym_f64(hipStream_t s, char tb, int64_t n, int64_t K, double alpha, const double* A, int64_t lda,
+                  const double* B, int64_t ldb, double beta, double* C, int64_t ldc, bool mirror, Arena& ws,
+                  int64_t skip0 = 0, int64_t skip1 = 0);
+size_t gemm_sym_workspace(int64_t n, int64_t K);
+
 // Workspace (bytes) gemm_f64 may need for a split-K launch of this shape.
 size_t gemm_f64_workspace(int64_t M, int64_t N, int64_t K);
 
@@ -210,6 +221,9 @@ void lincomb3_f64(hipStream_t s, int64_t n, int64_t ld, double a, const double* 
 void scale_f64(hipStream_t s, double* X, int64_t count, double alpha);
 // (U, V) -> (V - U, V + U) in place: U <- V - U, V <- V + U
 void pade_pm_f64(hipStream_t s, double* U, double* V, int64_t count);
+// *flag = 1 if X (n x n) differs from its transpose in any entry (a NaN does),
+// else 0
+void asymmetry_f64(hipStream_t s, const double* X, int64_t n, int64_t ld, double* flag);
 // column absolute sums -> colsum[n]; then device max -> out (1 double)
 void norm1_f64(hipStream_t s, const double* X, int64_t rows, int64_t cols, int64_t ld,
                double* colsum, double* out);
@@ -237,6 +251,13 @@ void lu_solve_f64(hipStream_t s, int64_t n, double* P, int64_t ldp, double* Q, i
                   int* info_dev);
 size_t lu_solve_workspace(int64_t n);
 size_t lu_solve_workspace(int64_t n, int64_t nrhs);
+
+// Symmetric positive definite P (spd.hip): out = P^-1 (full), P (lower triangle
+// read, ld even) is destroyed; *info_dev as above for a pivot that is not
+// positive.
+void spd_inverse_f64(hipStream_t s, int64_t n, double* P, int64_t ld, double* out, int64_t ldo, Arena& ws,
+                     int* info_dev);
+size_t spd_inverse_workspace(int64_t n);
 
 // A second stream beside the caller's, a ring of events for the waits
 // between the two, and a pinned, coherent host slot through which a one-thread

@@ -87,6 +87,21 @@ __global__ void colabs_kernel(const double* X, int64_t rows, int64_t cols, int64
   if (lane == 0) colsum[c] = s;
 }
 
+// Tile pairs (bj <= bi) of X against X^T; any mismatch sets *flag (every
+// writer writes the same value).
+__global__ void asymmetry_kernel(const double* X, int64_t n, int64_t ld, double* flag) {
+  __shared__ double tile[32][33];
+  const int64_t r0 = (int64_t)blockIdx.x * 32, c0 = (int64_t)blockIdx.y * 32;
+  if (c0 > r0) return;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
+  for (int j = ty; j < 32; j += 8) tile[j][tx] = (r0 + tx < n && c0 + j < n) ? X[r0 + tx + (c0 + j) * ld] : 0.0;
+  __syncthreads();
+  bool bad = false;
+  for (int j = ty; j < 32; j += 8)
+    if (c0 + tx < n && r0 + j < n) bad = bad || !(X[c0 + tx + (r0 + j) * ld] == tile[tx][j]);
+  if (bad) *flag = 1.0;
+}
+
 __global__ void max_kernel(const double* v, int64_t count, double* out) {
   __shared__ double sm[kT];
   double m = 0.0;
@@ -205,6 +220,14 @@ void lincomb3_f64(hipStream_t s, int64_t n, int64_t ld, double a, const double* 
   if (n <= 0) return;
   hipLaunchKernelGGL(lincomb3_kernel, dim3(grid_for(ld * n)), dim3(kT), 0, s, n, ld, a, X1, b, X2, c,
                      X3, d, Y);
+  DME_HIP(hipGetLastError());
+}
+
+void asymmetry_f64(hipStream_t s, const double* X, int64_t n, int64_t ld, double* flag) {
+  fill_f64(s, flag, 1, 1, 1, 0.0);
+  if (n <= 0) return;
+  const unsigned nt = (unsigned)cdiv(n, 32);
+  hipLaunchKernelGGL(asymmetry_kernel, dim3(nt, nt), dim3(kT), 0, s, X, n, ld, flag);
   DME_HIP(hipGetLastError());
 }
 

@@ -167,11 +167,16 @@ const int hi = lane >> 5, w = (lane >> 1) & (kBK - 1);
 // read.  Random operands, n x n x n: 66 TFLOP/s at 4096 and 70 at 8192 (50 and 51
 // with the slabs through registers behind bounds checks and two barriers a
 // slab); 4032 x 8128 x 64 added to C, bound by C's traffic, 132 us (240).
-template <int BM, int BN, bool TA, bool TB, bool VEC>
+// SYM: the result is known to be symmetric (M = N, BM = BN): the grid holds the
+// tiles of the lower triangle only, and entries below the diagonal are also
+// written above it (kSymMirror) or not (kSymLower); kSymLower leaves out rows
+// and columns [skip0, skip1).
+constexpr int kSymNone = 0, kSymLower = 1, kSymMirror = 2;
+template <int BM, int BN, bool TA, bool TB, bool VEC, int SYM = kSymNone>
 __global__ __launch_bounds__(kThreads, 2) void gemm_f64_kernel(
     int M, int N, int K, int kchunk, double alpha, const double* __restrict__ A, int64_t lda,
     const double* __restrict__ B, int64_t ldb, double beta, double* __restrict__ C, int64_t ldc,
-    double* __restrict__ partial) {
+    double* __restrict__ partial, int skip0, int skip1) {
   constexpr int WTM = BM / 2, WTN = BN / 2;  // wave tile
   constexpr int TM = WTM / 16, TN = WTN / 16;
   typedef Slab<TA, BM, VEC> SA;
@@ -182,8 +187,16 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_f64_kernel(
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave & 1, wn = wave >> 1;
-  const int m0 = blockIdx.x * BM;
-  const int n0 = blockIdx.y * BN;
+  int bi = blockIdx.x, bj = blockIdx.y;
+  if (SYM) {  // tile bi (bi + 1) / 2 + bj, bj <= bi
+    const int t = blockIdx.x;
+    bi = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+    while (bi * (bi + 1) / 2 > t) --bi;
+    while ((bi + 1) * (bi + 2) / 2 <= t) ++bi;
+    bj = t - bi * (bi + 1) / 2;
+  }
+  const int m0 = bi * BM;
+  const int n0 = bj * BN;
   const int kbeg = blockIdx.z * kchunk;
   const int kend = min(K, kbeg + kchunk);
   const int r16 = lane & 15;
@@ -248,7 +261,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_f64_kernel(
   double* const Cb = partial ? partial + (int64_t)blockIdx.z * M * N : C;
   const int64_t ldo = partial ? M : ldc;
   const int mw = m0 + wm * WTM, nw = n0 + wn * WTN;
-  const bool pairs = !TA && ldo % 2 == 0 && reinterpret_cast<uintptr_t>(Cb) % 16 == 0 && mw + WTM <= M;
+  const bool pairs = !TA && ldo % 2 == 0 && reinterpret_cast<uintptr_t>(Cb) % 16 == 0 && mw + WTM <= M &&
+                     (!SYM || (bi > bj && (mw + WTM <= skip0 || mw >= skip1) && (nw + WTN <= skip0 || nw >= skip1)));
   double old[2][4][TM];
   auto read_old = [&](int j, double (&o)[4][TM]) {
 #pragma unroll
@@ -291,7 +305,16 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_f64_kernel(
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
           const int m = mw + SA::row(i, r16);
-          if (m < M) c[m] = out[i];
+          bool put = m < M && (!SYM || m >= n);
+          if (SYM == kSymLower) put = put && !(m >= skip0 && m < skip1) && !(n >= skip0 && n < skip1);
+          if (put) c[m] = out[i];
+        }
+      }
+      if (SYM == kSymMirror && scaled) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          const int m = mw + SA::row(i, r16);
+          if (m < M && m > n) Cb[n + (int64_t)m * ldo] = out[i];
         }
       }
     }
@@ -324,6 +347,23 @@ __global__ void splitk_reduce_kernel(int M, int N, int nsplit, double alpha,
     const double out = alpha * s;
     *c = (beta == 0.0) ? out : out + beta * (*c);
   }
+}
+
+// The same for a symmetric result whose partials hold its lower tiles: C(i, j),
+// i >= j, and its mirror image.
+__global__ void splitk_reduce_sym_kernel(int n, int nsplit, double alpha, const double* __restrict__ partial,
+                                         double beta, double* __restrict__ C, int64_t ldc) {
+  const int64_t total = (int64_t)n * n;
+  const int j = blockIdx.y;
+  const int i = j + blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int64_t idx = i + (int64_t)j * n;
+  double v = 0.0;
+  for (int z = 0; z < nsplit; ++z) v += partial[z * total + idx];
+  v *= alpha;
+  if (beta != 0.0) v += beta * C[i + j * ldc];
+  C[i + j * ldc] = v;
+  C[j + i * ldc] = v;
 }
 
 // Small products (M, N <= kSmallMaxMN, K <= kSmallMaxK: the k x k products of
@@ -551,7 +591,7 @@ void launch_tile(hipStream_t s, int M, int N, int K, int nsplit, int kchunk, dou
   // both operands in 16-byte pieces or both in 4-byte ones
   auto kern = vec_ok(A, lda, TA, M) && vec_ok(B, ldb, !TB, N) ? gemm_f64_kernel<BM, BN, TA, TB, true>
                                                               : gemm_f64_kernel<BM, BN, TA, TB, false>;
-  hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, M, N, K, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
+  hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, M, N, K, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial, 0, 0);
 }
 
 template <int BM, int BN>
@@ -929,6 +969,70 @@ void gemm_f64(hipStream_t s, char ta, char tb, int64_t M, int64_t N, int64_t K, 
                        partial, beta, C, ldc);
     DME_HIP(hipGetLastError());
   }
+}
+
+// Symmetric results.  128 x 128 tiles where the lower triangle has one for every
+// CU, else 64 x 64 ones with K split until there are four a CU; up to
+// kSmallMaxMN rows the full small product is as fast.
+namespace {
+struct SymPlan {
+  int bm, nsplit, kchunk;
+};
+SymPlan sym_plan(int64_t n, int64_t K, bool split) {
+  SymPlan p{};
+  auto tiles = [&](int64_t b) { return cdiv(n, b) * (cdiv(n, b) + 1) / 2; };
+  p.bm = tiles(128) >= kMinTiles ? 128 : 64;
+  int64_t ns = 1;
+  if (split && tiles(p.bm) < kTargetBlocks && p.bm == 64 && K >= 2 * kMinKChunk)
+    ns = std::min<int64_t>(cdiv(kTargetBlocks, tiles(p.bm)), K / kMinKChunk);
+  const int64_t kc = cdiv(cdiv(K, ns), kBK) * kBK;
+  p.kchunk = (int)kc;
+  p.nsplit = (int)cdiv(K, kc);
+  return p;
+}
+}  // namespace
+
+size_t gemm_sym_workspace(int64_t n, int64_t K) {
+  const SymPlan p = sym_plan(n, K, true);
+  return std::max((p.nsplit > 1 ? (size_t)p.nsplit * n * n * sizeof(double) : 0) + 256, gemm_f64_workspace(n, n, K));
+}
+
+void gemm_sym_f64(hipStream_t s, char tb, int64_t n, int64_t K, double alpha, const double* A, int64_t lda,
+                  const double* B, int64_t ldb, double beta, double* C, int64_t ldc, bool mirror, Arena& ws,
+                  int64_t skip0, int64_t skip1) {
+  if (n <= 0) return;
+  const bool TB = (tb == 'T' || tb == 't');
+  if (mirror && n <= kSmallMaxMN) {
+    gemm_f64(s, 'N', tb, n, n, K, alpha, A, lda, B, ldb, beta, C, ldc, &ws);
+    return;
+  }
+  DME_REQUIRE(K >= 1 && n < (1ll << 31) && K < (1ll << 31) && vec_ok(A, lda, false, n) && vec_ok(B, ldb, !TB, n),
+              DME_EINTERNAL, "symmetric product: operands at odd leading dimensions");
+  const SymPlan p = sym_plan(n, K, mirror);
+  const size_t mark = ws.used;
+  double* partial = p.nsplit > 1 ? ws.get<double>((size_t)p.nsplit * n * n) : nullptr;
+  const int64_t nt = cdiv(n, p.bm);
+  const dim3 grid((unsigned)(nt * (nt + 1) / 2), 1, (unsigned)p.nsplit);
+  auto run = [&](auto kern) {
+    hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, (int)n, (int)n, (int)K, p.kchunk, alpha, A, lda, B, ldb, beta,
+                       C, ldc, partial, (int)skip0, (int)skip1);
+  };
+  if (mirror) {
+    DME_REQUIRE(!TB, DME_EINTERNAL, "symmetric product: form not built");
+    if (p.bm == 128) run(gemm_f64_kernel<128, 128, false, false, true, kSymMirror>);
+    else run(gemm_f64_kernel<64, 64, false, false, true, kSymMirror>);
+  } else {
+    DME_REQUIRE(TB, DME_EINTERNAL, "symmetric product: form not built");
+    if (p.bm == 128) run(gemm_f64_kernel<128, 128, false, true, true, kSymLower>);
+    else run(gemm_f64_kernel<64, 64, false, true, true, kSymLower>);
+  }
+  DME_HIP(hipGetLastError());
+  if (partial) {
+    hipLaunchKernelGGL(splitk_reduce_sym_kernel, dim3((unsigned)cdiv(n, 256), (unsigned)n), dim3(256), 0, s, (int)n,
+                       p.nsplit, alpha, partial, beta, C, ldc);
+    DME_HIP(hipGetLastError());
+  }
+  ws.used = mark;
 }
 
 }  // namespace dme

@@ -48,3 +48,21 @@ def test_expm_permuted_plane_rotations(ctx, n, theta):
     ref[j, i] = -np.sin(theta)
     assert (m, s) == (13, 0)
     assert float((E - ref).norm() / ref.norm()) < TOL
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 129, 257, 300, 513, 1030, 2049])
+@pytest.mark.parametrize("nrm", [5.0, 50.0])
+def test_expm_symmetric(ctx, n, nrm):
+    """An exactly symmetric operator: half products and the positive definite
+    denominator's inverse, at the edges of 64-row blocks and of the tiles."""
+    announce("expm symmetric", n, nrm)
+    G = np.random.default_rng(n).standard_normal((n, n))
+    X = G + G.T
+    X *= nrm / max(oracle.norm1(X), 1e-300) * (1.0 - 1e-12)
+    X = (X + X.T) / 2
+    E, m, s = ctx.expm(X, 1.0)
+    assert (m, s) == (oracle.expm_params(oracle.norm1(X)))
+    E = to_np(E)
+    assert rel_fro(E, oracle.expm(X)) < TOL
+    if n > 256:
+        assert np.array_equal(E, E.T)
