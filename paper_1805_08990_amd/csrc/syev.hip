@@ -38,6 +38,8 @@
 // reproduced to roundoff and the vectors are orthonormal to roundoff.
 #include "common.h"
 
+#include <type_traits>
+
 namespace dme {
 namespace {
 
@@ -46,6 +48,7 @@ constexpr int kRowLanes = 256;
 constexpr int kColGroups = kTriT / kRowLanes;
 constexpr double kOrtol = 1e-3;  // gaps below kOrtol ||T|| join a cluster
 constexpr int kInvitIters = 3;
+constexpr int kTriMinSteps = 8;  // steps a tile size of the reduction is worth
 constexpr int kInvitLdsMaxK = 2048;  // inverse-iteration arrays in LDS up to this k
 constexpr int kInvitArrays = 8;      // k-long arrays per inverse iteration
 
@@ -70,6 +73,19 @@ __device__ inline double group_sum_f64(double v) {
   if constexpr (G == 8) return group8_sum_f64(v);
   v += dpp_mov_f64<kDppXor1>(v);
   return v + dpp_mov_f64<kDppXor2>(v);
+}
+
+// Sum over the wave by two FP64 MFMAs with ones (row sums of the 16 x 4 operand,
+// then of the row sums; the same value in every lane): about 170 cycles from
+// operand to result against 370 for six DPP steps, each of which is a chain of
+// two moves and an addition.  For a wave whose chain is the critical one; it
+// holds its SIMD's matrix unit for 128 cycles.
+__device__ inline double wave_sum_mfma_f64(double v) {
+  typedef double v4 __attribute__((ext_vector_type(4)));
+  const v4 zero = v4{0.0, 0.0, 0.0, 0.0};
+  const v4 r = __builtin_amdgcn_mfma_f64_16x16x4f64(v, 1.0, zero, 0, 0, 0);
+  const v4 q = __builtin_amdgcn_mfma_f64_16x16x4f64((r[0] + r[1]) + (r[2] + r[3]), 1.0, zero, 0, 0, 0);
+  return q[0];
 }
 
 // Reduce-scatter steps over a half-wave (32 lanes).  rs16: lanes 0-15 of the
@@ -166,10 +182,10 @@ __device__ __forceinline__ void tile_rank2(double (&a)[RT][NC], const double* vr
 // tri_prep_kernel computes), by the whole workgroup from d and e in LDS;
 // red holds at least 4 x (waves) doubles.  Called after a barrier.
 __device__ inline void tri_bounds_block(const double* sd, const double* se, int k, double* e2, double* bounds,
-                                        double* red) {
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6, nw = blockDim.x >> 6;
+                                        double* red, int nthreads) {
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, nw = nthreads >> 6;
   double lo = INFINITY, hi = -INFINITY, me2 = 0.0, nrm = 0.0;
-  for (int i = t; i < k; i += blockDim.x) {
+  for (int i = t; i < k; i += nthreads) {
     const double el = (i > 0) ? fabs(se[i - 1]) : 0.0;
     const double er = (i + 1 < k) ? fabs(se[i]) : 0.0;
     lo = fmin(lo, sd[i] - el - er);
@@ -215,7 +231,7 @@ __device__ inline void tri_bounds_block(const double* sd, const double* se, int 
 // (h = 2 wave + half) and lane c of them holds the columns c + 32 m (m < NC),
 // so a half-wave holds whole rows.  Step j takes two barriers:
 //   product phase: p = tau A v by row sums (a reduce-scatter over the 32
-//     lanes), the per-wave parts of p^T v, and column j + 1 as it stands
+//     lanes), and column j + 1 as it stands
 //     (by symmetry the lane q & 31 of every half-wave holds its rows), all to
 //     LDS;
 //   update phase: every wave applies A -= v w^T + w v^T,
@@ -226,22 +242,39 @@ __device__ inline void tri_bounds_block(const double* sd, const double* se, int 
 // reflector (a wave sum, a reciprocal square root and a reciprocal) runs
 // beside the update.  The input Min is read once, into the registers; the
 // reflector of step j goes to A(j+2:, j) and d, e, tau as in tridiag_kernel.
-template <int NC, int RT>
-__global__ __launch_bounds__(32 * 32 * NC / RT) void tridiag_tiles_kernel(const double* Min, int64_t ldm,
-                                                                          double* A, int64_t lda, int k,
-                                                                          double* d, double* e, double* tau,
-                                                                          double* e2, double* bounds) {
+//
+// A tile holds dead rows and columns as the trailing part shrinks, and the
+// steps' FP64 issue is that of the whole tile, so the reduction moves to
+// smaller tiles (of fewer waves; the others end) when 128 and 64 rows are left:
+// the trailing part goes through A's own, still unused, place.  Per reduction,
+// with the reflector's shorter chain (MFMA wave sums, one third-order step a
+// root, no branch on tau): 264 us at k = 178 (322 with one tile size and DPP
+// sums), 90 at k of about 90 (108).
+template <int KM>
+struct TriLds {
+  static constexpr int KP = 64 * ((KM + 63) / 64);
+  double vbuf[2][KP];  // reflector of step j in vbuf[j & 1]
+  double tjs[2];       // and its tau
+  double pb[KP];       // p
+  double cb[KP];       // column j + 1 before the update of step j
+  double sd[KM], se[KM];  // d and e as formed, for the bounds at the end
+};
+
+// Steps 0 .. jend - 1 of a k x k matrix in tiles of NC x RT, by the first
+// NC 16 / RT waves; jend >= k - 2: to the end, else the trailing part (rows and
+// columns from jend on) is left in A.  All pointers are to the matrix's own
+// first entries.
+template <int NC, int RT, class Lds>
+__device__ __forceinline__ void tridiag_phase(const double* Min, int64_t ldm, double* A, int64_t lda, int k, int jend,
+                                              double* d, double* e, double* tau, Lds& S, double* sd, double* se) {
   constexpr int KM = 32 * NC;        // largest k
   constexpr int NW = KM / (2 * RT);  // waves: two RT-row tiles each
   static_assert(KM % (2 * RT) == 0 && NW <= 16 && RT % 2 == 0, "whole waves, at most 16, row pairs");
   constexpr int NC2 = (KM + 63) / 64;  // entries per lane of wave 0 when it forms a reflector
-  constexpr int KP = 64 * NC2;
-  __shared__ double vbuf[2][KP];  // reflector of step j in vbuf[j & 1]
-  __shared__ double tjs[2];       // and its tau
-  __shared__ double pb[KP];       // p
-  __shared__ double cb[KP];       // column j + 1 before the update of step j
-  __shared__ double wpart[NW];
-  __shared__ double sd[KM], se[KM];  // d and e as formed, for the bounds at the end
+  double* const pb = S.pb;
+  double* const cb = S.cb;
+  double* const tjs = S.tjs;
+  auto& vbuf = S.vbuf;
   const int t = threadIdx.x;
   const int lane = t & 63, wv = t >> 6;
   const int c = lane & 31;
@@ -263,7 +296,7 @@ __global__ __launch_bounds__(32 * 32 * NC / RT) void tridiag_tiles_kernel(const 
   // r = 1/sqrt(S) and n = S r: beta = -sign(alpha) n,
   // tau = (beta - alpha)/beta = 1 + |alpha| r and
   // 1/(alpha - beta) = sign(alpha)/(|alpha| + n), the reciprocal square root
-  // and the reciprocal from the hardware estimates by two Newton steps each.
+  // and the reciprocal from the hardware estimates by a third-order step each.
   auto form = [&](int q, const double (&y)[NC2], double dq, double alpha) {
     const bool refl = q + 2 < k;
     double s2 = 0.0;
@@ -272,20 +305,22 @@ __global__ __launch_bounds__(32 * 32 * NC / RT) void tridiag_tiles_kernel(const 
       const int l = lane + 64 * m;
       s2 += (l >= q + 2 && l < k) ? y[m] * y[m] : 0.0;
     }
-    s2 = wave_sum_f64(s2);
+    s2 = wave_sum_mfma_f64(s2);
     double beta = alpha, tq = 0.0, sc = 0.0;
     if (refl && s2 != 0.0) {
-      const double S = fma(alpha, alpha, s2), hS = 0.5 * S;
+      const double S = fma(alpha, alpha, s2);
+      // r (1 + e/2 + 3 e^2/8) and r (1 + e + e^2): third order in the estimates'
+      // relative errors of about 2^-23
       double r = __builtin_amdgcn_rsq(S);
-      r = r * fma(-hS * r, r, 1.5);
-      r = r * fma(-hS * r, r, 1.5);
+      const double er = fma(-S * r, r, 1.0);
+      r = fma(r * er, fma(er, 0.375, 0.5), r);
       const double n = S * r, aa = fabs(alpha);
       beta = -copysign(n, alpha);
       tq = fma(aa, r, 1.0);
       const double den = aa + n;
       double ri = __builtin_amdgcn_rcp(den);
-      ri = fma(ri, fma(-den, ri, 1.0), ri);
-      ri = fma(ri, fma(-den, ri, 1.0), ri);
+      const double ei = fma(-den, ri, 1.0);
+      ri = fma(ri, fma(ei, ei, ei), ri);
       sc = copysign(ri, alpha);
     }
     double vv[NC2];
@@ -326,13 +361,17 @@ __global__ __launch_bounds__(32 * 32 * NC / RT) void tridiag_tiles_kernel(const 
     form(0, y0, cb[0], k > 1 ? cb[1] : 0.0);
   }
   __syncthreads();
-  for (int j = 0; j + 2 < k; ++j) {
+  const int nsteps = min(jend, max(k - 2, 0));
+  const bool whole = nsteps == max(k - 2, 0);
+  for (int j = 0; j < nsteps; ++j) {
     const int r0 = j + 1, q = j + 1;
     const int mq = q >> 5;  // chunk of column q (chunks m < mq lie before the trailing part)
+    // (a step without a reflector has tau = 0 and a finite v: it runs through
+    // and changes nothing, which costs less than a branch on tau's arrival)
     const double tj = tjs[j & 1];
     const double* v = vbuf[j & 1];
     const bool live = wrow_last >= r0;  // wave-uniform
-    if (tj != 0.0) {                    // uniform across the workgroup
+    {
       double vC[NC];
 #pragma unroll
       for (int m = 0; m < NC; ++m) vC[m] = v[c + 32 * m];
@@ -348,9 +387,6 @@ __global__ __launch_bounds__(32 * 32 * NC / RT) void tridiag_tiles_kernel(const 
       }
       const bool lead = (c % SL) == 0;  // one lane per row
       if (lead && srow < RT) pb[rbase + srow] = pu;
-      const double vs = (srow < RT) ? v[rbase + min(srow, RT - 1)] : 0.0;
-      const double pv = wave_sum_f64(lead ? pu * vs : 0.0);  // both half-waves
-      if (lane == 0) wpart[wv] = pv;
     }
     if (live && c == (q & 31)) {
 #pragma unroll
@@ -361,37 +397,42 @@ __global__ __launch_bounds__(32 * 32 * NC / RT) void tridiag_tiles_kernel(const 
         }
     }
     __syncthreads();
-    double Kc = 0.0;
-    if (tj != 0.0) {
-      constexpr int G = NW <= 4 ? 4 : (NW <= 8 ? 8 : 16);  // NW <= 16
-      const int gi = lane & (G - 1);
-      const double pvt = group_sum_f64<G>(gi < NW ? wpart[gi] : 0.0);
-      Kc = 0.5 * tj * pvt;
-    }
-    if (wv == 0) {
-      // column q after step j: y_l = x_l - v_l w_q - w_l v_q with v_q = 1
-      // (the entry (l, q) of the tile update); unchanged when the step had no
-      // reflector.  Every load is issued before the arithmetic.
-      const bool upd = tj != 0.0;
-      const double pq = pb[q], vq1 = v[q + 1], pq1 = pb[q + 1], cq = cb[q], cq1 = cb[q + 1];
-      double xl[NC2], vl[NC2], pl[NC2];
+    // K = (tau/2) p^T v, by every wave that needs it from the whole vectors (the
+    // reflector's wave by the shorter chain)
+    double vl[NC2], pl[NC2];
 #pragma unroll
-      for (int m = 0; m < NC2; ++m) {
-        const int l = lane + 64 * m;
-        xl[m] = cb[l];
-        vl[m] = v[l];
-        pl[m] = pb[l];
-      }
+    for (int m = 0; m < NC2; ++m) {
+      vl[m] = v[lane + 64 * m];
+      pl[m] = pb[lane + 64 * m];
+    }
+    double pv = 0.0, Kc = 0.0;
+#pragma unroll
+    for (int m = 0; m < NC2; ++m) pv = fma(pl[m], vl[m], pv);
+    const bool reflects = wv == 0 && (whole || j + 1 < nsteps);  // (the next phase forms its own first reflector)
+    if (live && !reflects) Kc = 0.5 * tj * wave_sum_f64(pv);
+    if (reflects) {
+      // column q after step j: y_l = x_l - v_l w_q - w_l v_q with v_q = 1
+      // (the entry (l, q) of the tile update).  Every load is issued before the
+      // arithmetic, and the compiler is kept from moving one behind it.
+      double pq = pb[q], vq1 = v[q + 1], pq1 = pb[q + 1], cq = cb[q], cq1 = cb[q + 1];
+      double xl[NC2];
+#pragma unroll
+      for (int m = 0; m < NC2; ++m) xl[m] = cb[lane + 64 * m];
+      pin(pq);
+      pin(vq1);
+      pin(pq1);
+      pin(cq);
+      pin(cq1);
+      Kc = 0.5 * tj * wave_sum_mfma_f64(pv);
       const double wq = pq - Kc, wq1 = pq1 - Kc * vq1;
-      const double dq = upd ? fma(-1.0, wq, fma(-wq, 1.0, cq)) : cq;
-      const double alpha = upd ? fma(-vq1, wq, fma(-wq1, 1.0, cq1)) : cq1;
+      const double dq = fma(-1.0, wq, fma(-wq, 1.0, cq));
+      const double alpha = fma(-vq1, wq, fma(-wq1, 1.0, cq1));
       double y[NC2];
 #pragma unroll
-      for (int m = 0; m < NC2; ++m)
-        y[m] = upd ? fma(-vl[m], wq, fma(-(pl[m] - Kc * vl[m]), 1.0, xl[m])) : xl[m];
+      for (int m = 0; m < NC2; ++m) y[m] = fma(-vl[m], wq, fma(-(pl[m] - Kc * vl[m]), 1.0, xl[m]));
       form(q, y, dq, alpha);
     }
-    if (tj != 0.0 && live) {
+    if (live) {
       double vC2[NC], wC[NC];
 #pragma unroll
       for (int m = 0; m < NC; ++m) {
@@ -401,6 +442,20 @@ __global__ __launch_bounds__(32 * 32 * NC / RT) void tridiag_tiles_kernel(const 
       tile_rank2<NC, RT>(a, v + rbase, pb + rbase, Kc, vC2, wC);
     }
     __syncthreads();
+  }
+  if (!whole) {
+#pragma unroll
+    for (int u = 0; u < RT; ++u) {
+      const int i = rbase + u;
+#pragma unroll
+      for (int m = 0; m < NC; ++m)
+        if (i >= nsteps && i < k && c + 32 * m >= nsteps && c + 32 * m < k) A[c + 32 * m + (int64_t)i * lda] = a[u][m];
+    }
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
+    __syncthreads();
+    return;
   }
   // the last diagonal entry
   if (k - 1 >= rbase && k - 1 < rbase + RT) {
@@ -418,7 +473,54 @@ __global__ __launch_bounds__(32 * 32 * NC / RT) void tridiag_tiles_kernel(const 
     if (c == 0) tau[k - 1] = 0.0;
   }
   __syncthreads();
-  tri_bounds_block(sd, se, k, e2, bounds, pb);  // pb (KM >= 4 NW doubles) is free by now
+}
+
+template <int NC, int RT>
+__global__ __launch_bounds__(32 * 32 * NC / RT) void tridiag_tiles_kernel(const double* Min, int64_t ldm,
+                                                                          double* A, int64_t lda, int k,
+                                                                          double* d, double* e, double* tau,
+                                                                          double* e2, double* bounds) {
+  typedef TriLds<32 * NC> Lds;
+  __shared__ Lds S;
+  const int t = threadIdx.x;
+  int nthreads = 32 * 32 * NC / RT, o = 0;  // o: rows done
+  // the rows and columns from o on, which the last phase left in A
+  auto next = [&](auto nc, auto rt, int left) {
+    constexpr int N = decltype(nc)::value, T = decltype(rt)::value;
+    if (o > 0) {
+      nthreads = 32 * 32 * N / T;
+      if (t >= nthreads) return false;
+    }
+    const double* from = o > 0 ? A + o * (lda + 1) : Min;
+    const int stop = left > 0 ? k - o - left : k;
+    tridiag_phase<N, T>(from, o > 0 ? lda : ldm, A + o * (lda + 1), lda, k - o, stop, d + o, e + o, tau + o, S,
+                        S.sd + o, S.se + o);
+    o += stop;
+    return true;
+  };
+  using std::integral_constant;
+  typedef integral_constant<int, 8> R8;
+  // (a phase of a few steps does not pay for its hand-over)
+  if constexpr (NC > 4) {
+    if (k > 128 + kTriMinSteps)
+      if (!next(integral_constant<int, NC>(), integral_constant<int, RT>(), 128)) return;
+  }
+  if constexpr (NC >= 4) {
+    if (NC == 4 || o > 0) {
+      if (k > 64 + kTriMinSteps)
+        if (!next(integral_constant<int, 4>(), R8(), 64)) return;
+      if (o > 0) {
+        if (!next(integral_constant<int, 2>(), R8(), 0)) return;
+      } else {
+        next(integral_constant<int, 4>(), R8(), 0);
+      }
+    } else {
+      next(integral_constant<int, NC>(), integral_constant<int, RT>(), 0);
+    }
+  } else {
+    next(integral_constant<int, NC>(), integral_constant<int, RT>(), 0);
+  }
+  tri_bounds_block(S.sd, S.se, k, e2, bounds, S.pb, nthreads);  // pb (KP >= 4 NW doubles) is free by now
 }
 
 // Householder tridiagonalisation for k <= kTriMaxK, same outputs as
