@@ -248,7 +248,7 @@ struct LuWork;
 // n x nrhs (ld ldq).  Returns through *info_dev (device int): 0 ok, j+1 if pivot
 // j is exactly zero.
 void lu_solve_f64(hipStream_t s, int64_t n, double* P, int64_t ldp, double* Q, int64_t ldq, int64_t nrhs, Arena& ws,
-                  int* info_dev);
+                  int* info_dev, bool kept = false);
 size_t lu_solve_workspace(int64_t n);
 size_t lu_solve_workspace(int64_t n, int64_t nrhs);
 
@@ -319,7 +319,7 @@ size_t compress_workspace(int64_t n, int64_t k);
 // known (the stream's earlier work is done) and returns r.
 int64_t compress_f64(hipStream_t s, int64_t n, int64_t k, double* W, const double* Dhat, double tol,
                   int64_t max_rank, double* L, int64_t ldl, double* Dout, int64_t ldd,
-                  int64_t* rank_dev, int* flag_dev, Arena& ws);
+                  int64_t* rank_dev, int* flag_dev, Arena& ws, bool kept = false);
 // The same compression through the Gram matrix (gram.hip) for a symmetric
 // positive definite Dhat (ld lddh; dhat_diag: Dhat is diagonal): Dhat = F F^T,
 // G = F^T W^T W F, G = V Lam V^T truncated, L = W F V_I Lam_I^-1/2.  W (n x k,
@@ -359,7 +359,8 @@ int64_t compress_gram_f64(hipStream_t s, int64_t n, int64_t k, const double* W, 
                           double tol, int64_t max_rank, double* L, int64_t ldl, double* Dout, int64_t ldd,
                           int64_t* rank_dev, int* flag_dev, Arena& ws, int64_t rank_hint = 0,
                           const double* F_ready = nullptr, const int64_t* status_ready = nullptr,
-                          double* T_keep = nullptr, const std::function<void(hipEvent_t)>* beside = nullptr);
+                          double* T_keep = nullptr, const std::function<void(hipEvent_t)>* beside = nullptr,
+                          bool kept = false);
 // Launches the closed-form factor F (k x k, ld k) of a Dhat in the LowRankD
 // form on st, with its status in *status; returns false, launching nothing,
 // when the form's limits (m <= 8, r <= 256) do not hold.
@@ -384,8 +385,11 @@ inline int64_t rank_to_host(hipStream_t s, const int64_t* rank_dev) {
 // the bound auxiliary stream as soon as it is known (rank_seq set: the
 // sequence number for value_to_host_wait on the second stream; the value is
 // -1 when *rank_veto is nonzero).
+// kept: every rounding as in the eigensolver's first form, for the mixed mode
+// (see Solver::kept).
 struct SyevPost {
   bool signs = true;
+  bool kept = false;
   const int64_t* rank_veto = nullptr;
   int64_t* rank_seq = nullptr;
 };

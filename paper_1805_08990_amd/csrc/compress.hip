@@ -120,7 +120,7 @@ size_t compress_workspace(int64_t n, int64_t k) {
 
 int64_t compress_f64(hipStream_t s, int64_t n, int64_t k, double* W, const double* Dhat,
                      double tol, int64_t max_rank, double* L, int64_t ldl, double* Dout,
-                     int64_t ldd, int64_t* rank_dev, int* flag_dev, Arena& ws) {
+                     int64_t ldd, int64_t* rank_dev, int* flag_dev, Arena& ws, bool kept) {
   if (k <= 0 || n <= 0) {
     return 0;
   }
@@ -159,7 +159,9 @@ int64_t compress_f64(hipStream_t s, int64_t n, int64_t k, double* W, const doubl
 
   // ---------------- eigenpairs with truncation
   ws.used = mark_q;
-  syev_trunc_f64(s, kr, S, kr, tol, std::min(max_rank, kr), lam, V, kr, rank_dev, flag_dev, ws);
+  SyevPost post;
+  post.kept = kept;
+  syev_trunc_f64(s, kr, S, kr, tol, std::min(max_rank, kr), lam, V, kr, rank_dev, flag_dev, ws, post);
   const int64_t r = rank_to_host(s, rank_dev);
   if (r <= 0) {
     DME_HIP(hipStreamWaitEvent(s, qe_done, 0));  // the second stream still reads W

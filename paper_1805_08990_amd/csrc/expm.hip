@@ -16,7 +16,9 @@
 // function of it, so symmetric: its products then take half the work
 // (gemm_sym_f64), and step 4 is F = (V - U)^-1 (V + U) with the inverse of the
 // positive definite denominator (spd.hip).  Measured at n = 4096 with four
-// squarings: 20.0 ms against 36.2 for the general path.
+// squarings: 20.0 ms against 36.2 for the general path.  A caller that depends
+// on the last bit of E (kept; see Solver::kept) takes full products and the LU
+// in its kept form instead.
 #include "common.h"
 
 #include <cmath>
@@ -66,7 +68,7 @@ size_t expm_workspace(int64_t n) {
 
 // E = e^{tX}; X, E are n x n device matrices (contiguous), E must not alias X.
 void expm_f64(hipStream_t s, int64_t n, const double* X, double t, double* E, Arena& ws, int* m_out,
-              int* s_out, int* info_dev) {
+              int* s_out, int* info_dev, bool kept) {
   if (n <= 0) return;
   const int64_t ld = expm_ld(n);
   const size_t nn = (size_t)ld * n;
@@ -88,7 +90,7 @@ void expm_f64(hipStream_t s, int64_t n, const double* X, double t, double* E, Ar
   DME_HIP(hipMemcpyAsync(head, nrm_dev, sizeof(head), hipMemcpyDeviceToHost, s));
   DME_HIP(hipStreamSynchronize(s));
   const double nrm = head[0];
-  const bool sym = head[1] == 0.0;
+  const bool sym = head[1] == 0.0 && !kept;
   DME_REQUIRE(std::isfinite(nrm), DME_ENUMERIC, "expm: operator has non-finite entries");
   int m = 13, sc = 0;
   expm_params(nrm, &m, &sc);
@@ -146,7 +148,7 @@ void expm_f64(hipStream_t s, int64_t n, const double* X, double t, double* E, Ar
     mm(Y6, V, 0.0, T1);
     std::swap(cur, other);
   } else {
-    lu_solve_f64(s, n, U, ld, V, ld, n, ws, info_dev);
+    lu_solve_f64(s, n, U, ld, V, ld, n, ws, info_dev, kept);
   }
   // squaring phase
   for (int q = 0; q < sc; ++q) {

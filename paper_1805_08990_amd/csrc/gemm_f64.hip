@@ -131,25 +131,27 @@ const int hi = lane >> 5, w = (lane >> 1) & (kBK - 1);
       s[d] = k0 + k < kend ? v[u] : 0.0;
     }
   }
-  // fragments of T 16-row tiles from row w0 on, k = 8 h + 2 kq and + 1.  A tile
-  // is 16 consecutive rows (KC) or every other row of 32 (!KC).
+  // fragments of T 16-row tiles from row w0 on, k = 8 h + 4 e + kq (four
+  // consecutive k a MFMA, in order, so that a sum's rounding does not depend on
+  // how its operands lie in memory).  A tile is 16 consecutive rows (KC) or
+  // every other row of 32 (!KC).
   template <int T>
   static __device__ void frags(const double* s, int w0, int h, int r16, int kq, double (&f)[T][2]) {
     typedef double v2d __attribute__((ext_vector_type(2)));
     if (KC) {
 #pragma unroll
-      for (int i = 0; i < T; ++i) {
-        const int r = w0 + 16 * i + r16, c = (4 * h + kq) ^ ((r16 >> 1) & 7);
-        const v2d v = *reinterpret_cast<const v2d*>(s + r * kBK + 2 * c);
-        f[i][0] = v.x;
-        f[i][1] = v.y;
-      }
+      for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int r = w0 + 16 * i + r16, c = (4 * h + 2 * e + (kq >> 1)) ^ ((r16 >> 1) & 7);
+          f[i][e] = s[r * kBK + 2 * c + (kq & 1)];
+        }
     } else {
 #pragma unroll
       for (int e = 0; e < 2; ++e)
 #pragma unroll
         for (int i = 0; i < T; i += 2) {
-          const v2d v = *reinterpret_cast<const v2d*>(s + (8 * h + 2 * kq + e) * B + w0 + 16 * i + 2 * r16);
+          const v2d v = *reinterpret_cast<const v2d*>(s + (8 * h + 4 * e + kq) * B + w0 + 16 * i + 2 * r16);
           f[i][e] = v.x;
           f[i + 1][e] = v.y;
         }
@@ -163,8 +165,7 @@ const int hi = lane >> 5, w = (lane >> 1) & (kBK - 1);
 // 64 cycles for a 16 x 16 x 4 step, so a wave's 64 x 64 block is 4096 cycles of
 // MFMA per slab and the kernel is bound by it as long as nothing else stops the
 // waves: the slabs go to LDS without registers or guards between, into two
-// buffers with one barrier a slab, and a lane takes two k or two rows per LDS
-// read.  Random operands, n x n x n: 66 TFLOP/s at 4096 and 70 at 8192 (50 and 51
+// buffers with one barrier a slab.  Random operands, n x n x n: 66 TFLOP/s at 4096 and 70 at 8192 (50 and 51
 // with the slabs through registers behind bounds checks and two barriers a
 // slab); 4032 x 8128 x 64 added to C, bound by C's traffic, 132 us (240).
 // SYM: the result is known to be symmetric (M = N, BM = BN): the grid holds the

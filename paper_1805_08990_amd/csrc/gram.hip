@@ -479,7 +479,7 @@ int64_t compress_gram_f64(hipStream_t s, int64_t n, int64_t k, const double* W, 
                           double tol, int64_t max_rank, double* L, int64_t ldl, double* Dout, int64_t ldd,
                           int64_t* rank_dev, int* flag_dev, Arena& ws, int64_t rank_hint,
                           const double* F_ready, const int64_t* status_ready, double* T_keep,
-                          const std::function<void(hipEvent_t)>* beside) {
+                          const std::function<void(hipEvent_t)>* beside, bool kept) {
   if (k <= 0 || n <= 0) return 0;
   const size_t mark = ws.used;
   double* Fw = ws.get<double>((size_t)k * k);
@@ -538,6 +538,7 @@ int64_t compress_gram_f64(hipStream_t s, int64_t n, int64_t k, const double* W, 
   int64_t seq_rank = 0;
   SyevPost post;
   post.signs = false;
+  post.kept = kept;
   post.rank_veto = fstatus;
   post.rank_seq = &seq_rank;
   syev_trunc_f64(s, k, S, k, tol, std::min(max_rank, k), lam, V, k, rank_dev, flag_dev, ws, post);

@@ -18,6 +18,9 @@
 //   cols   : the remaining columns and the right-hand sides: both panels' row
 //            moves and U12 = inv(L11) A12.
 //   A22    : A22 - L21 U12 and the same of the right-hand sides (FP64 MFMA).
+// The kept form rounds every entry as the method's first implementation did (a
+// division per multiplier, block triangles applied through their inverses by
+// products), for callers whose results depend on the last bit (expm.hip).
 // What bounds it: up to n of a few thousand the chain of panels (a launch pair
 // per column takes 18 us a column; at n = 4096 a 64-column block of this takes
 // 180 us and the whole solve 17 ms instead of 95); beyond that the trailing
@@ -57,7 +60,8 @@ __device__ inline double quad_bcast_f64(double v) {
 // so the loop body is short and has no register indexed by the step (the
 // straight-line form ran at the rate its instructions could be fetched).
 // Entries shifted in past the end are never used.  4 * groups steps.
-template <int NJ, bool SCALE, class Put>
+// DIVIDE: sR holds the divisors themselves (0: the entry becomes 0).
+template <int NJ, bool SCALE, bool DIVIDE = false, class Put>
 __device__ inline void quad_substitute(double (&x)[NJ], int groups, const double* sM, const double* sR, int q, Put put) {
 #pragma unroll 1
   for (int k = 0; k < groups; ++k) {
@@ -66,7 +70,8 @@ __device__ inline void quad_substitute(double (&x)[NJ], int groups, const double
       constexpr int S = decltype(sc)::value;
       double p = quad_bcast_f64<S>(x[0]);
       if (SCALE) {
-        p *= sR[4 * k + S];
+        if (DIVIDE) p = sR[4 * k + S] != 0.0 ? p / sR[4 * k + S] : 0.0;
+        else p *= sR[4 * k + S];
         if (q == S) x[0] = p;
       }
 #pragma unroll
@@ -310,7 +315,7 @@ __global__ __launch_bounds__(64) void lu_select_kernel(const double* __restrict_
 // multipliers of the first one.  Only the place itself is written, and moved
 // rows come from the panel's top, which is not.
 constexpr int kQuadT = 128;
-template <int O>
+template <int O, bool KEPT>
 __global__ __launch_bounds__(kQuadT) void lu_rows_kernel(double* __restrict__ A, int64_t lda, int n, int j0, int jb,
                                                          int jb2, const double* __restrict__ blk,
                                                          const Moves* __restrict__ mv) {
@@ -334,7 +339,7 @@ __global__ __launch_bounds__(kQuadT) void lu_rows_kernel(double* __restrict__ A,
   }
   if (tid < kPW) {
     const double d = blk[(O + tid) * (kNB + 1)];
-    sR[tid] = tid < jb && d != 0.0 ? 1.0 / d : 0.0;
+    sR[tid] = tid < jb && d != 0.0 ? (KEPT ? d : 1.0 / d) : 0.0;
     sdst[tid] = mv->dst[tid];
     ssrc[tid] = mv->src[tid];
   }
@@ -364,7 +369,7 @@ __global__ __launch_bounds__(kQuadT) void lu_rows_kernel(double* __restrict__ A,
 #pragma unroll
     for (int j = 0; j < kPW / 4; ++j) Ai[(int64_t)(4 * j + q) * lda] = y[j];
   }
-  quad_substitute<NJ, true>(x, kPW / 4, sM, sR, q, [&](int k, double v) {
+  quad_substitute<NJ, true, KEPT>(x, kPW / 4, sM, sR, q, [&](int k, double v) {
     if (4 * k + q < jb) Ai[(int64_t)(O + 4 * k + q) * lda] = v;
   });
   if (O == 0) {
@@ -392,10 +397,11 @@ __device__ inline void move_rows(double* col, const Moves& mv, int q) {
     if (d[j] >= 0) col[d[j]] = w[j];
   __threadfence_block();  // another lane of the quad reads what this one moved
 }
+// tmp (optional): the moved block rows go there unsolved, jb x (ncols + nq).
 __global__ __launch_bounds__(kQuadT) void lu_cols_kernel(double* X, int64_t ldx, int c0, int ncols, double* Q,
                                                          int64_t ldq, int nq, int j0, int jb,
                                                          const double* __restrict__ blk,
-                                                         const Moves* __restrict__ mv) {
+                                                         const Moves* __restrict__ mv, double* __restrict__ tmp) {
   __shared__ double sM[kNB * kNB + kNB];
   __shared__ Moves smv[2];
   const int jb1 = min(jb, kPW), jb2 = jb - jb1;
@@ -444,6 +450,15 @@ __global__ __launch_bounds__(kQuadT) void lu_cols_kernel(double* X, int64_t ldx,
     if (4 * j + q >= jb2) x[kPW / 4 + j] = 0.0;
   }
   if (jb2 > 0) move_rows(col, smv[1], q);
+  if (tmp) {
+#pragma unroll
+    for (int j = 0; j < kNB / 4; ++j) {
+      // (the panels' rows are 32 apart in x, whatever jb is)
+      const int t = 4 * j + q;
+      if (t < jb) tmp[t + (int64_t)id * jb] = x[j];
+    }
+    return;
+  }
   quad_substitute<kNB / 4, false>(x, kNB / 4, sM, nullptr, q, [&](int k, double v) {
     if (4 * k + q < jb) col[j0 + 4 * k + q] = v;
   });
@@ -491,6 +506,53 @@ __global__ __launch_bounds__(kQuadT) void lu_back_kernel(double* __restrict__ Q,
   });
 }
 
+// Xl = inverse of the block's unit lower triangle (KEPT form): a column of it
+// per quad, by the sums of each entry in ascending order.
+__global__ __launch_bounds__(4 * kNB) void lu_linv_kernel(const double* __restrict__ blk, int jb, double* __restrict__ Xl) {
+  __shared__ double sM[kNB * kNB + kNB];
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int u = 0; u < kNB / 4; ++u) {
+    const int e = tid + u * 4 * kNB, i = e % kNB, c = e / kNB;
+    double v = blk[e];
+    pin(v);
+    sM[e] = (i < jb && c < i) ? v : 0.0;
+  }
+  __syncthreads();
+  const int q = tid & 3, c = tid >> 2;
+  double x[kNB / 4];
+#pragma unroll
+  for (int j = 0; j < kNB / 4; ++j) x[j] = 4 * j + q == c ? 1.0 : 0.0;
+  quad_substitute<kNB / 4, false>(x, kNB / 4, sM, nullptr, q, [&](int k, double v) {
+    if (4 * k + q < jb && c < jb) Xl[4 * k + q + c * jb] = v;
+  });
+}
+
+// Xu = inverses of the blocks' upper triangles (KEPT form), one block a
+// workgroup, a column per thread, each entry one dot product in ascending order.
+__global__ __launch_bounds__(kNB) void lu_uinv_kernel(const double* __restrict__ blks, int n, double* __restrict__ Xu) {
+  __shared__ double s[kNB * kNB];
+  __shared__ double x[kNB * (kNB + 1)];
+  const int b = min(kNB, n - (int)blockIdx.x * kNB);
+  const double* T = blks + (int64_t)blockIdx.x * kNB * kNB;
+  double* X = Xu + (int64_t)blockIdx.x * kNB * kNB;
+  for (int idx = threadIdx.x; idx < kNB * kNB; idx += kNB) s[idx] = T[idx];
+  __syncthreads();
+  const int c = threadIdx.x;
+  if (c < b) {
+    double* xc = x + c * (kNB + 1);
+    for (int r = 0; r < b; ++r) xc[r] = 0.0;
+    xc[c] = 1.0 / s[c + c * kNB];
+    for (int r = c - 1; r >= 0; --r) {
+      double acc = 0.0;
+      for (int t = r + 1; t <= c; ++t) acc += s[r + t * kNB] * xc[t];
+      xc[r] = -acc / s[r + r * kNB];
+    }
+  }
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < b * b; idx += kNB) X[idx] = x[idx % b + (idx / b) * (kNB + 1)];
+}
+
 // players a level of the tournament hands on
 int64_t lu_named(int64_t players) { return cdiv(players, kLeaf) * kPW; }
 
@@ -502,6 +564,8 @@ size_t lu_solve_workspace(int64_t n, int64_t nrhs) {
   size_t b = 0;
   b += 2 * ((size_t)lu_named(n) * sizeof(int) + 256);                     // tournament lists
   b += (size_t)kPW * kLeaf * sizeof(double);                              // multipliers of a deciding level
+  b += (size_t)kNB * (n + std::max<int64_t>(nrhs, 0)) * sizeof(double) + 256;  // moved block rows (kept form)
+  b += (size_t)(cdiv(n, kNB) + 1) * kNB * kNB * sizeof(double) + 512;     // inverse blocks (kept form)
   b += 2 * sizeof(Moves) + 256;                                           // row moves of a block
   b += (size_t)cdiv(n, kNB) * kNB * kNB * sizeof(double) + 256;           // diagonal blocks
   b += std::max({gemm_f64_workspace(n, n, kNB), gemm_f64_workspace(n, std::max<int64_t>(nrhs, 1), kNB)}) + 256;
@@ -509,15 +573,18 @@ size_t lu_solve_workspace(int64_t n, int64_t nrhs) {
 }
 
 void lu_solve_f64(hipStream_t s, int64_t n, double* A, int64_t lda, double* Q, int64_t ldq, int64_t nrhs, Arena& ws,
-                  int* info_dev) {
+                  int* info_dev, bool kept) {
   if (n <= 0) return;
   DME_REQUIRE(n < (1ll << 30) && nrhs < (1ll << 30), DME_EINVAL, "LU: dimensions too large");
   int* lists[2] = {ws.get<int>(lu_named(n)), ws.get<int>(lu_named(n))};
   Moves* mv = ws.get<Moves>(2);
   double* lbuf = ws.get<double>((size_t)kPW * kLeaf);
   double* blks = ws.get<double>((size_t)cdiv(n, kNB) * kNB * kNB);
-  const size_t mark = ws.used;
   const int nq = (int)std::max<int64_t>(nrhs, 0);
+  double* tmp = kept ? ws.get<double>((size_t)kNB * (n + nq)) : nullptr;
+  double* linv = kept ? ws.get<double>((size_t)kNB * kNB) : nullptr;
+  double* uinv = kept ? ws.get<double>((size_t)cdiv(n, kNB) * kNB * kNB) : nullptr;
+  const size_t mark = ws.used;
 
   // pivots of panel o (its rows start at j0 + o) and the factor of its block
   auto select = [&](int64_t j0, int o, int jb, int jb2, double* blk) {
@@ -545,7 +612,7 @@ void lu_solve_f64(hipStream_t s, int64_t n, double* A, int64_t lda, double* Q, i
     select(j0, 0, jb1, jb2, blk);
     const int64_t below1 = n - j0 - jb1;
     if (below1 > 0) {
-      hipLaunchKernelGGL((lu_rows_kernel<0>), dim3((unsigned)cdiv(below1, kQuadT / 4)), dim3(kQuadT), 0, s, A, lda, (int)n,
+      hipLaunchKernelGGL((kept ? lu_rows_kernel<0, true> : lu_rows_kernel<0, false>), dim3((unsigned)cdiv(below1, kQuadT / 4)), dim3(kQuadT), 0, s, A, lda, (int)n,
                          (int)j0, jb1, jb2, blk, mv);
       DME_HIP(hipGetLastError());
     }
@@ -553,15 +620,24 @@ void lu_solve_f64(hipStream_t s, int64_t n, double* A, int64_t lda, double* Q, i
     if (jb2 > 0) {
       select(j0, kPW, jb2, 0, blk);
       if (rest > 0) {
-        hipLaunchKernelGGL((lu_rows_kernel<kPW>), dim3((unsigned)cdiv(rest, kQuadT / 4)), dim3(kQuadT), 0, s, A, lda, (int)n,
+        hipLaunchKernelGGL((kept ? lu_rows_kernel<kPW, true> : lu_rows_kernel<kPW, false>), dim3((unsigned)cdiv(rest, kQuadT / 4)), dim3(kQuadT), 0, s, A, lda, (int)n,
                            (int)j0, jb2, 0, blk, mv + 1);
         DME_HIP(hipGetLastError());
       }
     }
     if (rest + nq > 0) {
       hipLaunchKernelGGL(lu_cols_kernel, dim3((unsigned)cdiv(rest + nq, kQuadT / 4)), dim3(kQuadT), 0, s, A, lda,
-                         (int)(j0 + jb), (int)rest, Q, ldq, nq, (int)j0, jb, blk, mv);
+                         (int)(j0 + jb), (int)rest, Q, ldq, nq, (int)j0, jb, blk, mv, tmp);
       DME_HIP(hipGetLastError());
+    }
+    if (kept && rest + nq > 0) {
+      hipLaunchKernelGGL(lu_linv_kernel, dim3(1), dim3(4 * kNB), 0, s, blk, jb, linv);
+      DME_HIP(hipGetLastError());
+      ws.used = mark;
+      if (rest > 0)
+        gemm_f64(s, 'N', 'N', jb, rest, jb, 1.0, linv, jb, tmp, jb, 0.0, A + j0 + (j0 + jb) * lda, lda, &ws);
+      ws.used = mark;
+      if (nq > 0) gemm_f64(s, 'N', 'N', jb, nq, jb, 1.0, linv, jb, tmp + (size_t)jb * rest, jb, 0.0, Q + j0, ldq, &ws);
     }
     if (rest > 0) {
       const double* L21 = A + (j0 + jb) + j0 * lda;
@@ -575,10 +651,19 @@ void lu_solve_f64(hipStream_t s, int64_t n, double* A, int64_t lda, double* Q, i
     }
   }
   // backward substitution U X = Y
+  if (nq > 0 && kept) {
+    hipLaunchKernelGGL(lu_uinv_kernel, dim3((unsigned)cdiv(n, kNB)), dim3(kNB), 0, s, blks, (int)n, uinv);
+    DME_HIP(hipGetLastError());
+  }
   if (nq > 0)
     for (int64_t b = cdiv(n, kNB) - 1; b >= 0; --b) {
       const int64_t j0 = b * kNB;
       const int jb = (int)std::min<int64_t>(kNB, n - j0);
+      if (kept) {
+        copy_f64(s, Q + j0, ldq, tmp, jb, jb, nq);
+        ws.used = mark;
+        gemm_f64(s, 'N', 'N', jb, nq, jb, 1.0, uinv + b * kNB * kNB, jb, tmp, jb, 0.0, Q + j0, ldq, &ws);
+      } else
       hipLaunchKernelGGL(lu_back_kernel, dim3((unsigned)cdiv(nq, kQuadT / 4)), dim3(kQuadT), 0, s, Q, ldq, nq, (int)j0, jb,
                          blks + b * kNB * kNB);
       DME_HIP(hipGetLastError());

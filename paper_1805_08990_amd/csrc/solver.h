@@ -17,7 +17,7 @@ namespace dme {
 void expm_params(double nrm1, int* m, int* s);
 size_t expm_workspace(int64_t n);
 void expm_f64(hipStream_t s, int64_t n, const double* X, double t, double* E, Arena& ws, int* m_out,
-              int* s_out, int* info_dev);
+              int* s_out, int* info_dev, bool kept = false);
 // K-point Gauss-Legendre nodes and weights on [0, t] (ascending nodes).
 void gauss_legendre(int K, double t, std::vector<double>& nodes, std::vector<double>& weights);
 
@@ -125,6 +125,11 @@ struct Solver {
   DevBuf L[2], D[2];
   int cur = 0;
   int64_t r = 0;
+  // DME_MIXED: the split-BF16 products turn a difference in the last bit of what
+  // they are given into one of 1e-9 within a few steps, so such a solve keeps
+  // every rounding of the operators, the quadrature factor and the compressions
+  // as it has always been, and its results stay the same to the bit
+  bool kept() const { return opts.precision == DME_MIXED; }
   bool d_diag = true;  // D is diagonal (a compression's output; T3 fills it)
   // D = diag(lamT3) - t3 Z Z^T with Z in ZT3 (T3 applied to a diagonal D)
   bool d_lowrank = false;

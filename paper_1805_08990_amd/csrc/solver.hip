@@ -362,7 +362,7 @@ std::shared_ptr<OperatorSet> build_operator_set(hipStream_t s, int64_t n, const 
   Arena ews;
   ews.reserve(expm_workspace(n));
   op->E.ensure((size_t)n * n * sizeof(double));
-  expm_f64(s, n, AT, t, op->E.as<double>(), ews, nullptr, nullptr, info_dev);
+  expm_f64(s, n, AT, t, op->E.as<double>(), ews, nullptr, nullptr, info_dev, precision == DME_MIXED);
   if (precision == DME_MIXED) {
     op->mix = mixed_op_new();
     mixed_op_build(s, n, op->E.as<double>(), *op->mix);
@@ -374,7 +374,7 @@ std::shared_ptr<OperatorSet> build_operator_set(hipStream_t s, int64_t n, const 
     for (int q = 0; q < K; ++q) {
       ews.reset();
       op->nodes[q].ensure((size_t)n * n * sizeof(double));
-      expm_f64(s, n, AT, nodes[q], op->nodes[q].as<double>(), ews, nullptr, nullptr, info_dev);
+      expm_f64(s, n, AT, nodes[q], op->nodes[q].as<double>(), ews, nullptr, nullptr, info_dev, precision == DME_MIXED);
     }
   }
   DME_HIP(hipEventRecord(b, s));
@@ -516,7 +516,7 @@ void Solver::build_quadrature(double t) {
       ews.reserve(expm_workspace(n));
       for (int q = 0; q < K; ++q) {
         ews.reset();
-        expm_f64(s, n, ATp, nodes[q], Ek.as<double>(), ews, nullptr, nullptr, flag_dev() + 1);
+        expm_f64(s, n, ATp, nodes[q], Ek.as<double>(), ews, nullptr, nullptr, flag_dev() + 1, kept());
         node_product(Ek.as<double>(), q);
       }
     }
@@ -531,7 +531,7 @@ void Solver::build_quadrature(double t) {
   f.D.ensure((size_t)kq * kq * sizeof(double));
   ws.reset();
   f.r = compress_f64(s, n, kq, Wd, Dh, opts.tol, std::min<int64_t>(kq, n), f.L.as<double>(), n,
-                     f.D.as<double>(), 0, rank_dev(), flag_dev(), ws);
+                     f.D.as<double>(), 0, rank_dev(), flag_dev(), ws, kept());
   rank_quad = std::max(rank_quad, f.r);
   check_flags("quadrature factor");
 }
@@ -728,7 +728,7 @@ void Solver::compress_into(int64_t k, int ncopies, double ahead_t) {
   int64_t rn = compress_gram_f64(s, n, k, W.as<double>(), n, Dhat.as<double>(), k, d_diag,
                                  d_lowrank ? &lr : nullptr, opts.tol, max_rank, Ln(), n, Dn(), 0, rank_dev(),
                                  flag_dev(), ws, r, Fr, Fs,  // the rank before: the guess for the new one
-                                 rows_b > 0 ? Tk.as<double>() : nullptr, rows_b > 0 ? &beside : nullptr);
+                                 rows_b > 0 ? Tk.as<double>() : nullptr, rows_b > 0 ? &beside : nullptr, kept());
   const double kk = (double)k;
   if (rn >= 0) {
     // W^T W 2 n k^2, L = W T 2 n k r', the k x k products and eigenproblem ~ 14 k^3
@@ -744,7 +744,7 @@ void Solver::compress_into(int64_t k, int ncopies, double ahead_t) {
   } else {
     ws.reset();
     rn = compress_f64(s, n, k, W.as<double>(), Dhat.as<double>(), opts.tol, max_rank, Ln(), n, Dn(), 0,
-                      rank_dev(), flag_dev(), ws);
+                      rank_dev(), flag_dev(), ws, kept());
     // Householder QR 2 n k^2 - 2/3 k^3, Q application 4 n k r', small eigenproblem ~ 10 k^3
     mark_end(1, ev, 2.0 * n * kk * kk + 4.0 * n * kk * rn + 10.0 * kk * kk * kk,
              8.0 * (2.0 * n * kk + 2.0 * n * rn));

@@ -255,16 +255,19 @@ struct TriLds {
   static constexpr int KP = 64 * ((KM + 63) / 64);
   double vbuf[2][KP];  // reflector of step j in vbuf[j & 1]
   double tjs[2];       // and its tau
+  double wpart[16];    // per-wave parts of p^T v (KEPT)
   double pb[KP];       // p
   double cb[KP];       // column j + 1 before the update of step j
   double sd[KM], se[KM];  // d and e as formed, for the bounds at the end
 };
 
+// KEPT: one tile size, p^T v by waves, DPP sums and two Newton steps a root, the
+// rounding of the kernel's first form.
 // Steps 0 .. jend - 1 of a k x k matrix in tiles of NC x RT, by the first
 // NC 16 / RT waves; jend >= k - 2: to the end, else the trailing part (rows and
 // columns from jend on) is left in A.  All pointers are to the matrix's own
 // first entries.
-template <int NC, int RT, class Lds>
+template <int NC, int RT, bool KEPT, class Lds>
 __device__ __forceinline__ void tridiag_phase(const double* Min, int64_t ldm, double* A, int64_t lda, int k, int jend,
                                               double* d, double* e, double* tau, Lds& S, double* sd, double* se) {
   constexpr int KM = 32 * NC;        // largest k
@@ -305,22 +308,33 @@ __device__ __forceinline__ void tridiag_phase(const double* Min, int64_t ldm, do
       const int l = lane + 64 * m;
       s2 += (l >= q + 2 && l < k) ? y[m] * y[m] : 0.0;
     }
-    s2 = wave_sum_mfma_f64(s2);
+    s2 = KEPT ? wave_sum_f64(s2) : wave_sum_mfma_f64(s2);
     double beta = alpha, tq = 0.0, sc = 0.0;
     if (refl && s2 != 0.0) {
       const double S = fma(alpha, alpha, s2);
       // r (1 + e/2 + 3 e^2/8) and r (1 + e + e^2): third order in the estimates'
       // relative errors of about 2^-23
       double r = __builtin_amdgcn_rsq(S);
-      const double er = fma(-S * r, r, 1.0);
-      r = fma(r * er, fma(er, 0.375, 0.5), r);
+      if constexpr (KEPT) {
+        const double hS = 0.5 * S;
+        r = r * fma(-hS * r, r, 1.5);
+        r = r * fma(-hS * r, r, 1.5);
+      } else {
+        const double er = fma(-S * r, r, 1.0);
+        r = fma(r * er, fma(er, 0.375, 0.5), r);
+      }
       const double n = S * r, aa = fabs(alpha);
       beta = -copysign(n, alpha);
       tq = fma(aa, r, 1.0);
       const double den = aa + n;
       double ri = __builtin_amdgcn_rcp(den);
-      const double ei = fma(-den, ri, 1.0);
-      ri = fma(ri, fma(ei, ei, ei), ri);
+      if constexpr (KEPT) {
+        ri = fma(ri, fma(-den, ri, 1.0), ri);
+        ri = fma(ri, fma(-den, ri, 1.0), ri);
+      } else {
+        const double ei = fma(-den, ri, 1.0);
+        ri = fma(ri, fma(ei, ei, ei), ri);
+      }
       sc = copysign(ri, alpha);
     }
     double vv[NC2];
@@ -387,6 +401,11 @@ __device__ __forceinline__ void tridiag_phase(const double* Min, int64_t ldm, do
       }
       const bool lead = (c % SL) == 0;  // one lane per row
       if (lead && srow < RT) pb[rbase + srow] = pu;
+      if constexpr (KEPT) {
+        const double vs = (srow < RT) ? v[rbase + min(srow, RT - 1)] : 0.0;
+        const double pw = wave_sum_f64(lead ? pu * vs : 0.0);  // both half-waves
+        if (lane == 0) S.wpart[wv] = pw;
+      }
     }
     if (live && c == (q & 31)) {
 #pragma unroll
@@ -409,7 +428,13 @@ __device__ __forceinline__ void tridiag_phase(const double* Min, int64_t ldm, do
 #pragma unroll
     for (int m = 0; m < NC2; ++m) pv = fma(pl[m], vl[m], pv);
     const bool reflects = wv == 0 && (whole || j + 1 < nsteps);  // (the next phase forms its own first reflector)
-    if (live && !reflects) Kc = 0.5 * tj * wave_sum_f64(pv);
+    if constexpr (KEPT) {
+      constexpr int G = NW <= 4 ? 4 : (NW <= 8 ? 8 : 16);  // NW <= 16
+      const int gi = lane & (G - 1);
+      Kc = 0.5 * tj * group_sum_f64<G>(gi < NW ? S.wpart[gi] : 0.0);
+    } else if (live && !reflects) {
+      Kc = 0.5 * tj * wave_sum_f64(pv);
+    }
     if (reflects) {
       // column q after step j: y_l = x_l - v_l w_q - w_l v_q with v_q = 1
       // (the entry (l, q) of the tile update).  Every load is issued before the
@@ -423,7 +448,7 @@ __device__ __forceinline__ void tridiag_phase(const double* Min, int64_t ldm, do
       pin(pq1);
       pin(cq);
       pin(cq1);
-      Kc = 0.5 * tj * wave_sum_mfma_f64(pv);
+      if constexpr (!KEPT) Kc = 0.5 * tj * wave_sum_mfma_f64(pv);
       const double wq = pq - Kc, wq1 = pq1 - Kc * vq1;
       const double dq = fma(-1.0, wq, fma(-wq, 1.0, cq));
       const double alpha = fma(-vq1, wq, fma(-wq1, 1.0, cq1));
@@ -475,7 +500,7 @@ __device__ __forceinline__ void tridiag_phase(const double* Min, int64_t ldm, do
   __syncthreads();
 }
 
-template <int NC, int RT>
+template <int NC, int RT, bool KEPT = false>
 __global__ __launch_bounds__(32 * 32 * NC / RT) void tridiag_tiles_kernel(const double* Min, int64_t ldm,
                                                                           double* A, int64_t lda, int k,
                                                                           double* d, double* e, double* tau,
@@ -493,7 +518,7 @@ __global__ __launch_bounds__(32 * 32 * NC / RT) void tridiag_tiles_kernel(const 
     }
     const double* from = o > 0 ? A + o * (lda + 1) : Min;
     const int stop = left > 0 ? k - o - left : k;
-    tridiag_phase<N, T>(from, o > 0 ? lda : ldm, A + o * (lda + 1), lda, k - o, stop, d + o, e + o, tau + o, S,
+    tridiag_phase<N, T, KEPT>(from, o > 0 ? lda : ldm, A + o * (lda + 1), lda, k - o, stop, d + o, e + o, tau + o, S,
                         S.sd + o, S.se + o);
     o += stop;
     return true;
@@ -501,6 +526,11 @@ __global__ __launch_bounds__(32 * 32 * NC / RT) void tridiag_tiles_kernel(const 
   using std::integral_constant;
   typedef integral_constant<int, 8> R8;
   // (a phase of a few steps does not pay for its hand-over)
+  if constexpr (KEPT) {
+    next(integral_constant<int, NC>(), integral_constant<int, RT>(), 0);
+    tri_bounds_block(S.sd, S.se, k, e2, bounds, S.pb, nthreads);
+    return;
+  }
   if constexpr (NC > 4) {
     if (k > 128 + kTriMinSteps)
       if (!next(integral_constant<int, NC>(), integral_constant<int, RT>(), 128)) return;
@@ -1717,18 +1747,17 @@ void syev_trunc_f64(hipStream_t s, int64_t k, const double* M, int64_t ldm, doub
     fill_f64(s, e, 1, 1, 1, 0.0);
     fill_f64(s, tau, 1, 1, 1, 0.0);
   } else {
+    auto run_tiles = [&](auto kern, int threads) {
+      hipLaunchKernelGGL(kern, dim3(1), dim3(threads), 0, s, M, ldm, A, k, ki, d, e, tau, e2, bounds);
+    };
     if (k <= 64) {
-      hipLaunchKernelGGL((tridiag_tiles_kernel<2, 8>), dim3(1), dim3(256), 0, s, M, ldm, A, k, ki, d, e, tau,
-                         e2, bounds);
+      run_tiles(post.kept ? tridiag_tiles_kernel<2, 8, true> : tridiag_tiles_kernel<2, 8>, 256);
     } else if (k <= 128) {
-      hipLaunchKernelGGL((tridiag_tiles_kernel<4, 8>), dim3(1), dim3(512), 0, s, M, ldm, A, k, ki, d, e, tau,
-                         e2, bounds);
+      run_tiles(post.kept ? tridiag_tiles_kernel<4, 8, true> : tridiag_tiles_kernel<4, 8>, 512);
     } else if (k <= 160) {
-      hipLaunchKernelGGL((tridiag_tiles_kernel<5, 8>), dim3(1), dim3(640), 0, s, M, ldm, A, k, ki, d, e, tau,
-                         e2, bounds);
+      run_tiles(post.kept ? tridiag_tiles_kernel<5, 8, true> : tridiag_tiles_kernel<5, 8>, 640);
     } else if (k <= 192) {
-      hipLaunchKernelGGL((tridiag_tiles_kernel<6, 12>), dim3(1), dim3(512), 0, s, M, ldm, A, k, ki, d, e, tau,
-                         e2, bounds);
+      run_tiles(post.kept ? tridiag_tiles_kernel<6, 12, true> : tridiag_tiles_kernel<6, 12>, 512);
     } else if (k <= kTriMaxK) {
       const size_t lds = (size_t)(3 + kTriT / 64) * k * sizeof(double);
       hipLaunchKernelGGL(tridiag_small_kernel, dim3(1), dim3(kTriT), lds, s, A, k, ki, d, e, tau);
