@@ -28,8 +28,9 @@
 //      orth_kernel      : one workgroup per remaining cluster orthonormalises
 //                         its vectors (right-looking modified Gram-Schmidt,
 //                         two passes).
-//   6. backtr_kernel    : Q = H_0 ... H_{k-3} formed one wave per column, on a
-//                         second stream beside steps 2-5; then V = Q Z (GEMM).
+//   6. form_q_kernel    : Q = H_0 ... H_{k-3} formed one wave per column (in
+//                         registers for k <= 192, backtr_kernel otherwise), on
+//                         a second stream beside steps 2-5; then V = Q Z (GEMM).
 //
 // An inverse-iteration vector is off its eigenvector by O(u ||M|| / gap) in
 // the directions of nearby eigenvectors; orthonormalising a cluster mixes its
@@ -798,12 +799,8 @@ __global__ void tri_prep_kernel(const double* d, const double* e, int k, double*
   }
 }
 
-// Sturm counts (eigenvalues of the tridiagonal (d, e) strictly below x) at
-// two shifts x1 < x2 at once (two independent recurrences interleaved, so
-// each hides the other's latency).  1/q comes from the
-// hardware reciprocal refined by one Newton step; the count only needs the
-// signs of q, which such a perturbation (a relative change of a few ulps of
-// the pivots, i.e. of d) leaves as correct as the exact division.
+// 1/q from the hardware reciprocal refined by one Newton step (a relative
+// change of a few ulps of the pivots, i.e. of d).
 __device__ inline double rcp_f64(double q) {
 #if defined(__HIP_DEVICE_COMPILE__)
   double r = __builtin_amdgcn_rcp(q);
@@ -814,7 +811,66 @@ __device__ inline double rcp_f64(double q) {
 #endif
 }
 
-__device__ inline void sturm_count2(const double* __restrict__ d, const double* __restrict__ e2, int k,
+// binary exponent of v (0 for zero, infinities and NaN)
+__device__ inline int ilogb_fast(double v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_frexp_exp(v);
+#else
+  return 0;
+#endif
+}
+
+// Sturm counts (eigenvalues of the tridiagonal (d, e) below x) at two shifts at
+// once, as the sign changes of the leading principal minors
+//   p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}
+// of T - x I (Givens 1954).  No division: a row is one dependent fused
+// multiply-add, against a reciprocal and its Newton step for the pivot ratios
+// p_i / p_{i-1}, whose rounding moves the entries of T by as much.  rows[i] holds
+// (d_i, e_{i-1}^2) of T scaled by a power of two to norm about one (xs the scaled
+// shifts), kp = k rounded up to eight with rows that change no sign; the pair
+// (p_i, p_{i-1}) is scaled to below one every eight rows, which the next eight
+// rows' LDS reads run under.  The sign changes go through a shift register.
+__device__ inline void sturm_minor2(const double2* rows, int kp, double xs1, double xs2, int& c1, int& c2) {
+  auto hi = [](double v) { return (uint32_t)((uint64_t)__double_as_longlong(v) >> 32); };
+  double a0 = 0.0, b0 = 0.0, a1 = 1.0, b1 = 1.0;
+  int n1 = 0, n2 = 0;
+  double2 cur[8], nxt[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) cur[u] = rows[u];
+#pragma unroll 2
+  for (int i = 0; i < kp; i += 8) {
+    const int in = min(i + 8, kp - 8);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) nxt[u] = rows[in + u];
+    uint32_t ra = 0, rb = 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const double a2 = fma(cur[u].x - xs1, a1, -(cur[u].y * a0));
+      const double b2 = fma(cur[u].x - xs2, b1, -(cur[u].y * b0));
+      ra = (ra << 1) | ((hi(a2) ^ hi(a1)) >> 31);
+      rb = (rb << 1) | ((hi(b2) ^ hi(b1)) >> 31);
+      a0 = a1;
+      a1 = a2;
+      b0 = b1;
+      b1 = b2;
+    }
+    const int ea = -ilogb_fast(fmax(fabs(a0), fabs(a1))), eb = -ilogb_fast(fmax(fabs(b0), fabs(b1)));
+    a0 = ldexp(a0, ea);
+    a1 = ldexp(a1, ea);
+    b0 = ldexp(b0, eb);
+    b1 = ldexp(b1, eb);
+    n1 += __popc(ra);
+    n2 += __popc(rb);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) cur[u] = nxt[u];
+  }
+  c1 = n1;
+  c2 = n2;
+}
+
+// The same two counts through the pivot ratios p_i / p_{i-1}, each with its
+// reciprocal (SyevPost::kept).
+__device__ inline void sturm_ratio2(const double* __restrict__ d, const double* __restrict__ e2, int k,
                                     double x1, double x2, double pivmin, int& c1, int& c2) {
   double q1 = d[0] - x1, q2 = d[0] - x2;
   if (fabs(q1) < pivmin) q1 = -pivmin;
@@ -841,27 +897,46 @@ __device__ inline void sturm_count2(const double* __restrict__ d, const double* 
 // 512-fold (four waves gain 9 bits a round where one gains 7, for the same
 // Sturm-count work per wave).  Each wave's first point above the index goes
 // through LDS and one barrier.  Stops at the width the reduction determines the
-// eigenvalue to.  d and e2 are read with scalar loads (the same entry for
-// every lane of a wave).
+// eigenvalue to.  RATIO counts by the pivot ratios, d and e2 read with scalar
+// loads (the same entry for every lane of a wave): for k past kBisMaxK, and for
+// SyevPost::kept.  Otherwise the scaled rows are in LDS (16 bytes a row) and
+// counted by minors.  Every e^2 is then at least 2^-120 of ||T||^2, which moves
+// no eigenvalue by more than 2^-60 ||T|| and keeps a zero minor from ending the
+// sequence.  Six rounds of k rows bound it: 43 us at k = 178 and 27 at 96, against
+// 74 and 35 by ratios (which wait for a scalar load every few rows, too).
+constexpr int kBisMaxK = 2048;
 constexpr int kBisWaves = 4;
+template <bool RATIO>
 __global__ __launch_bounds__(64 * kBisWaves) void bisect_wg_kernel(const double* __restrict__ d,
                                                                    const double* __restrict__ e2, int k,
                                                                    const double* __restrict__ bounds,
                                                                    double* lam) {
   constexpr int P = 128 * kBisWaves;  // points per round
+  extern __shared__ double2 bis_rows[];
   __shared__ int first[2][2][kBisWaves];  // [round parity][half][wave]: first point above, or P
   const int i = blockIdx.x;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   double lo = bounds[0], hi = bounds[1];
   const double pivmin = bounds[2];
   const double atol = DBL_EPSILON * bounds[3] + 2.0 * DBL_MIN;
+  const int es = RATIO ? 0 : -ilogb_fast(bounds[3]), kp = (k + 7) & ~7;
+  if constexpr (!RATIO) {
+    const double floor2 = bounds[3] > 0.0 ? 0x1p-120 : 0.0;
+    for (int j = t; j < kp; j += 64 * kBisWaves) {
+      const double dj = d[min(j, k - 1)], ej = ldexp(e2[max(min(j, k - 1) - 1, 0)], 2 * es);
+      const double e2j = (j > 0 && j < k) ? (ej < floor2 ? floor2 : ej) : 0.0;
+      bis_rows[j] = make_double2(j < k ? ldexp(dj, es) : 4.0, e2j);
+    }
+    __syncthreads();
+  }
   for (int it = 0; it < 64; ++it) {
     if (hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + atol) break;
     const double h = (hi - lo) / (double)P;
     const double x1 = lo + h * (double)(t + 1);
     const double x2 = (t < P / 2 - 1) ? lo + h * (double)(t + P / 2 + 1) : hi;
     int c1, c2;
-    sturm_count2(d, e2, k, x1, x2, pivmin, c1, c2);
+    if constexpr (RATIO) sturm_ratio2(d, e2, k, x1, x2, pivmin, c1, c2);
+    else sturm_minor2(bis_rows, kp, ldexp(x1, es), ldexp(x2, es), c1, c2);
     const uint64_t m1 = __ballot(c1 > i);
     const uint64_t m2 = __ballot((t == P / 2 - 1) || c2 > i);  // hi is always above
     const int par = it & 1;
@@ -1676,6 +1751,90 @@ __global__ __launch_bounds__(64 * kBtCols) void backtr_kernel(const double* A, i
   for (int i = lane; i < k; i += 64) V[i + (int64_t)c * ldv] = z[i];
 }
 
+// Q = H_0 ... H_{k-3} for k <= 64 NS (NS <= 3, the range of the register-tiled
+// reductions): one wave a column, which stays in registers, row lane + 64 s in
+// z[s].  A reflector is then three multiply-adds, a wave sum and three more
+// multiply-adds; the one after it is read from LDS meanwhile, and the next chunk
+// of kBtChunk from HBM while a chunk is applied.  H_j leaves e_c alone for
+// j >= c, so a block starts at its last column's first reflector.  A serial chain
+// over the reflectors bounds it: 50 us at k = 178 against 124 for backtr_kernel
+// (column in LDS, DPP sum; kept for larger k and for SyevPost::kept), 26 against
+// 40 at k = 96, which is less than the eigenvalue work beside it.
+template <int NS>
+__global__ __launch_bounds__(64 * kBtCols) void form_q_kernel(const double* __restrict__ A, int64_t lda,
+                                                              const double* __restrict__ tau, int k,
+                                                              double* __restrict__ Q, int64_t ldq) {
+  constexpr int kPer = kBtChunk / kBtCols;  // reflectors a wave stages of a chunk
+  __shared__ double vch[2][kBtChunk][64 * NS];
+  __shared__ double tch[2][kBtChunk];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int c = blockIdx.x * kBtCols + wv;
+  const int jtop = min(k - 3, (int)blockIdx.x * kBtCols + kBtCols - 2);
+  double z[NS], st[kPer][NS], tst = 0.0;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) z[s] = (lane + 64 * s == c) ? 1.0 : 0.0;
+  // the chunk of reflectors jlo .. jlo + kBtChunk - 1, at clamped addresses; the
+  // unit entries and the zeros (above them, past k, past jtop) come with store()
+  auto load = [&](int jlo) {
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const double* col = A + (int64_t)min(jlo + wv + kBtCols * q, k - 1) * lda;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) st[q][s] = col[min(lane + 64 * s, k - 1)];
+    }
+    tst = tau[min(jlo + (int)(threadIdx.x & (kBtChunk - 1)), k - 1)];
+  };
+  auto store = [&](int jlo, double (*vb)[64 * NS], double* tb) {
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int j = jlo + wv + kBtCols * q;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int i = lane + 64 * s;
+        double v = st[q][s];
+        pin(v);
+        v = (i > j + 1 && i < k && j <= jtop) ? v : 0.0;
+        vb[wv + kBtCols * q][i] = (i == j + 1) ? 1.0 : v;
+      }
+    }
+    double tv = tst;
+    pin(tv);
+    if (threadIdx.x < kBtChunk) tb[threadIdx.x] = (jlo + (int)threadIdx.x <= jtop) ? tv : 0.0;
+  };
+  const int nch = jtop / kBtChunk + 1;
+  if (jtop >= 0) load((nch - 1) * kBtChunk);
+  for (int ch = nch - 1; ch >= 0 && jtop >= 0; --ch) {
+    double(*vb)[64 * NS] = vch[ch & 1];
+    store(ch * kBtChunk, vb, tch[ch & 1]);
+    __syncthreads();
+    if (ch > 0) load((ch - 1) * kBtChunk);
+    double v[NS], tj = tch[ch & 1][kBtChunk - 1];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) v[s] = vb[kBtChunk - 1][lane + 64 * s];
+#pragma unroll 1
+    for (int jj = kBtChunk - 1; jj >= 0; --jj) {
+      const int jn = max(jj - 1, 0);
+      double vn[NS], tn = tch[ch & 1][jn];
+#pragma unroll
+      for (int s = 0; s < NS; ++s) vn[s] = vb[jn][lane + 64 * s];
+      double part = v[0] * z[0];
+#pragma unroll
+      for (int s = 1; s < NS; ++s) part = fma(v[s], z[s], part);
+      part = wave_sum_mfma_f64(part);
+      const double f = (tj == 0.0) ? 0.0 : -tj * part;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) z[s] = fma(f, v[s], z[s]);
+#pragma unroll
+      for (int s = 0; s < NS; ++s) v[s] = vn[s];
+      tj = tn;
+    }
+  }
+  if (c < k)
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (lane + 64 * s < k) Q[lane + 64 * s + (int64_t)c * ldq] = z[s];
+}
+
 // Sign convention of the eigenvectors: in each column c < keep[0] of V the
 // largest |entry| is positive (the first one on ties).  One wave per column.
 __global__ __launch_bounds__(64) void sign_columns_kernel(double* V, int64_t ldv, int k, const int64_t* keep) {
@@ -1772,14 +1931,18 @@ void syev_trunc_f64(hipStream_t s, int64_t k, const double* M, int64_t ldm, doub
   AuxStream& ax = aux_stream();
   DME_HIP(hipStreamWaitEvent(ax.s2, ax.record(s), 0));
   {
-    const dim3 bt_grid((unsigned)cdiv(k, kBtCols));
-    if (k <= kBtLdsMaxK)
-      hipLaunchKernelGGL(backtr_kernel<true>, bt_grid, dim3(64 * kBtCols),
+    const dim3 bt_grid((unsigned)cdiv(k, kBtCols)), bt_block(64 * kBtCols);
+    if (k <= 192 && !post.kept) {
+      auto kern = k <= 64 ? form_q_kernel<1> : k <= 128 ? form_q_kernel<2> : form_q_kernel<3>;
+      hipLaunchKernelGGL(kern, bt_grid, bt_block, 0, ax.s2, A, k, tau, ki, Qm, k);
+    } else if (k <= kBtLdsMaxK) {
+      hipLaunchKernelGGL(backtr_kernel<true>, bt_grid, bt_block,
                          (size_t)(kBtCols + kBtChunk) * k * sizeof(double), ax.s2, A, k, tau, ki,
                          (const double*)nullptr, k, keep_dev, ki, Qm, k);
-    else
-      hipLaunchKernelGGL(backtr_kernel<false>, bt_grid, dim3(64 * kBtCols), 0, ax.s2, A, k, tau, ki,
+    } else {
+      hipLaunchKernelGGL(backtr_kernel<false>, bt_grid, bt_block, 0, ax.s2, A, k, tau, ki,
                          (const double*)nullptr, k, keep_dev, ki, Qm, k);
+    }
     DME_HIP(hipGetLastError());
   }
   const hipEvent_t q_done = ax.record(ax.s2);
@@ -1787,7 +1950,11 @@ void syev_trunc_f64(hipStream_t s, int64_t k, const double* M, int64_t ldm, doub
     hipLaunchKernelGGL(tri_prep_kernel, dim3(1), dim3(256), 0, s, d, e, ki, e2, bounds);
     DME_HIP(hipGetLastError());
   }
-  hipLaunchKernelGGL(bisect_wg_kernel, dim3((unsigned)k), dim3(64 * kBisWaves), 0, s, d, e2, ki, bounds, lam);
+  if (post.kept || k > kBisMaxK)
+    hipLaunchKernelGGL(bisect_wg_kernel<true>, dim3((unsigned)k), dim3(64 * kBisWaves), 0, s, d, e2, ki, bounds, lam);
+  else
+    hipLaunchKernelGGL(bisect_wg_kernel<false>, dim3((unsigned)k), dim3(64 * kBisWaves),
+                       (size_t)((k + 7) & ~7) * sizeof(double2), s, d, e2, ki, bounds, lam);
   DME_HIP(hipGetLastError());
   const unsigned nkeep_sel = (unsigned)std::min<int64_t>(k, max_keep);
   int* cl_of = ws.get<int>(k);
