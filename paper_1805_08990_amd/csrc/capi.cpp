@@ -4,6 +4,7 @@
 #include <functional>
 #include <memory>
 #include <new>
+#include <set>
 
 #include "ctx.h"
 
@@ -15,7 +16,21 @@ void fail(int code, const std::string& msg) { throw Error{code, msg}; }
 
 void DevBuf::alloc(size_t b) {
   if (b == 0) b = 256;
+  pool = bound_pool();
+  if (pool) {
+    b = (b + 4095) & ~size_t(4095);
+    size_t got = b;
+    if ((p = pool->take(&got)) != nullptr) {
+      bytes = got;
+      return;
+    }
+  }
   hipError_t e = hipMalloc(&p, b);
+  if (e != hipSuccess) {  // with what the pools hold idle
+    (void)hipGetLastError();
+    DevicePool::trim_all();
+    e = hipMalloc(&p, b);
+  }
   if (e != hipSuccess) {
     p = nullptr;
     bytes = 0;
@@ -25,11 +40,125 @@ void DevBuf::alloc(size_t b) {
   bytes = b;
 }
 
+namespace {
+thread_local std::shared_ptr<DevicePool> g_pool;
+thread_local int g_quiet = 0;
+}  // namespace
+
 void DevBuf::release() {
-  if (p && own) (void)hipFree(p);
+  if (p && own) {
+    if (pool) {
+      if (g_quiet == 0) pool->wait();
+      pool->give(p, bytes);
+    } else {
+      (void)hipFree(p);
+    }
+  }
+  pool.reset();
   p = nullptr;
   bytes = 0;
   own = true;
+}
+
+PoolBinding::PoolBinding(const std::shared_ptr<DevicePool>& pool) : prev_(std::move(g_pool)) { g_pool = pool; }
+PoolBinding::~PoolBinding() { g_pool = std::move(prev_); }
+const std::shared_ptr<DevicePool>& bound_pool() { return g_pool; }
+QuietRelease::QuietRelease() { ++g_quiet; }
+QuietRelease::~QuietRelease() { --g_quiet; }
+
+namespace {
+// the pools there are, for trim_all(); never destroyed, since a context may
+// outlive the statics at process exit
+struct PoolList {
+  std::mutex mu;
+  std::set<DevicePool*> all;
+};
+PoolList& pool_list() {
+  static PoolList* l = new PoolList;
+  return *l;
+}
+}  // namespace
+
+DevicePool::DevicePool(int device, size_t max_idle) : device_(device), max_idle_(max_idle) {
+  std::lock_guard<std::mutex> g(pool_list().mu);
+  pool_list().all.insert(this);
+}
+
+DevicePool::~DevicePool() {
+  {
+    std::lock_guard<std::mutex> g(pool_list().mu);
+    pool_list().all.erase(this);
+  }
+  trim();
+}
+
+void DevicePool::trim_all() {
+  std::lock_guard<std::mutex> g(pool_list().mu);
+  for (DevicePool* p : pool_list().all) p->trim();
+}
+
+void DevicePool::wait() const {
+  int cur = 0;
+  (void)hipGetDevice(&cur);
+  if (cur != device_) (void)hipSetDevice(device_);
+  (void)hipDeviceSynchronize();
+  if (cur != device_) (void)hipSetDevice(cur);
+}
+
+void* DevicePool::take(size_t* bytes) {
+  std::lock_guard<std::mutex> g(mu_);
+  auto it = blocks_.lower_bound(*bytes);
+  if (it == blocks_.end() || it->first > *bytes + *bytes / 4 + (64u << 10)) return nullptr;
+  void* p = it->second;
+  *bytes = it->first;
+  idle_ -= it->first;
+  blocks_.erase(it);
+  return p;
+}
+
+void DevicePool::give(void* p, size_t bytes) {
+  {
+    std::lock_guard<std::mutex> g(mu_);
+    if (idle_ + bytes <= max_idle_) try {
+        blocks_.emplace(bytes, p);
+        idle_ += bytes;
+        return;
+      } catch (const std::exception&) {  // no host memory for the entry: free the block
+      }
+  }
+  (void)hipFree(p);
+}
+
+void DevicePool::trim() {
+  std::multimap<size_t, void*> all;
+  std::vector<std::unique_ptr<AuxStream>> aux;
+  {
+    std::lock_guard<std::mutex> g(mu_);
+    all.swap(blocks_);
+    aux.swap(aux_);
+    idle_ = 0;
+  }
+  for (auto& b : all) (void)hipFree(b.second);
+}
+
+void DevicePool::take_aux(AuxStream& a) {
+  std::lock_guard<std::mutex> g(mu_);
+  if (aux_.empty()) return;
+  a.adopt(*aux_.back());
+  aux_.pop_back();
+}
+
+void DevicePool::give_aux(AuxStream& a) {
+  constexpr size_t kMaxAux = 16;
+  std::lock_guard<std::mutex> g(mu_);
+  if (a.device != device_ || aux_.size() >= kMaxAux) return;
+  try {
+    aux_.push_back(std::make_unique<AuxStream>());
+  } catch (const std::exception&) {
+    return;  // the caller destroys it
+  }
+  a.drop_events();
+  aux_.back()->adopt(a);
 }
 
 KernelTimer*& kernel_timer() {
@@ -115,6 +244,7 @@ int solve_impl(dme_ctx* ctx, const dme_problem* prob, const dme_opts* opts, int 
     DME_REQUIRE(prob && opts && out, DME_EINVAL, "null argument");
     *out = nullptr;
     DME_HIP(hipSetDevice(ctx->device));
+    dme::PoolBinding pool(ctx->pool);
     dme::Solver sv;
     sv.s = ctx->stream;
     sv.device = ctx->device;
@@ -159,6 +289,7 @@ int dme_create(dme_ctx** ctx, int device, void* stream) {
     c->stream = static_cast<hipStream_t>(stream);
     c->flags.ensure(64);
     dme::noalloc_scratch_init(device);
+    c->pool = std::make_shared<dme::DevicePool>(device, dme::kPoolIdle);
     *ctx = c.release();
   });
 }
@@ -187,6 +318,7 @@ int dme_solver_create(dme_ctx* ctx, const dme_problem* prob, const dme_opts* opt
     DME_REQUIRE(prob && opts && out, DME_EINVAL, "null argument");
     *out = nullptr;
     DME_HIP(hipSetDevice(ctx->device));
+    dme::PoolBinding pool(ctx->pool);
     auto sv = std::make_unique<dme_solver>();
     sv->ctx = ctx;
     sv->sv.s = ctx->stream;

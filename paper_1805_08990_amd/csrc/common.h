@@ -9,6 +9,9 @@
 #include <cmath>
 #include <cstdint>
 #include <functional>
+#include <map>
+#include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -37,21 +40,85 @@ struct Error {
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Device buffer owned by the library (hipMalloc / hipFree).
+struct AuxStream;
+
+// Device blocks (and auxiliary streams) that the solves of one context, or of
+// one server, leave to the next one: a solve's buffers cost a driver call and
+// often a page table update each to allocate, and hipFree waits for the whole
+// device (4 of the 36 ms of a DRE solve at n = 1024, 7 of 24 of a GDRE solve at
+// n = 2025, 3 of the 18 a served request takes).  A block is handed out again only for a
+// request of nearly its size.  Idle blocks are bounded by max_idle bytes; what
+// goes beyond is freed, and all of it when the pool goes or any allocation of
+// the library fails.  Safe to use from several threads.
+//
+// Work that used a block has to be over when it is given back, whatever stream
+// it ran on: DevBuf::release() waits for the device as hipFree does, unless
+// the owner has synchronised its streams and says so (QuietRelease).  What a
+// block holds when it is handed out is undefined, as with hipMalloc.
+class DevicePool {
+ public:
+  DevicePool(int device, size_t max_idle);
+  ~DevicePool();
+  DevicePool(const DevicePool&) = delete;
+  DevicePool& operator=(const DevicePool&) = delete;
+  // an idle block of at least *bytes (its size in *bytes), or null
+  void* take(size_t* bytes);
+  void give(void* p, size_t bytes);
+  void trim();  // free every idle block and stream set
+  static void trim_all();  // ... of every pool of the process
+  void wait() const;       // for all work on the pool's device
+  // an idle auxiliary stream set into `a` (which has none), if there is one;
+  // back again once its streams are synchronised (without its events, which
+  // may be recorded on a stream that goes before the pool does)
+  void take_aux(AuxStream& a);
+  void give_aux(AuxStream& a);
+
+ private:
+  int device_;
+  size_t max_idle_, idle_ = 0;
+  std::mutex mu_;
+  std::multimap<size_t, void*> blocks_;
+  std::vector<std::unique_ptr<AuxStream>> aux_;
+};
+// Buffers the calling thread allocates come from `pool` while this lives.
+class PoolBinding {
+ public:
+  explicit PoolBinding(const std::shared_ptr<DevicePool>& pool);
+  ~PoolBinding();
+  PoolBinding(const PoolBinding&) = delete;
+  PoolBinding& operator=(const PoolBinding&) = delete;
+
+ private:
+  std::shared_ptr<DevicePool> prev_;
+};
+const std::shared_ptr<DevicePool>& bound_pool();
+// The calling thread's releases need no wait: the streams whose work used the
+// buffers are synchronised.
+struct QuietRelease {
+  QuietRelease();
+  ~QuietRelease();
+  QuietRelease(const QuietRelease&) = delete;
+  QuietRelease& operator=(const QuietRelease&) = delete;
+};
+
+// Device buffer owned by the library (hipMalloc / hipFree, or a pool's block).
 // A buffer attached with attach() is borrowed: release() forgets it.
 struct DevBuf {
   void* p = nullptr;
   size_t bytes = 0;
   bool own = true;
+  std::shared_ptr<DevicePool> pool;
   DevBuf() = default;
   explicit DevBuf(size_t b) { alloc(b); }
   DevBuf(const DevBuf&) = delete;
   DevBuf& operator=(const DevBuf&) = delete;
-  DevBuf(DevBuf&& o) noexcept : p(o.p), bytes(o.bytes), own(o.own) { o.p = nullptr; o.bytes = 0; o.own = true; }
+  DevBuf(DevBuf&& o) noexcept : p(o.p), bytes(o.bytes), own(o.own), pool(std::move(o.pool)) {
+    o.p = nullptr; o.bytes = 0; o.own = true;
+  }
   DevBuf& operator=(DevBuf&& o) noexcept {
     if (this != &o) {
       release();
-      p = o.p; bytes = o.bytes; own = o.own;
+      p = o.p; bytes = o.bytes; own = o.own; pool = std::move(o.pool);
       o.p = nullptr; o.bytes = 0; o.own = true;
     }
     return *this;
@@ -275,6 +342,7 @@ struct AuxStream {
   };
   int device = -1;
   hipStream_t s2 = nullptr;
+  hipStream_t s3 = nullptr;  // a third stream, created by an owner that wants one
   std::vector<hipEvent_t> ev;
   size_t next = 0;
   Slot* slot = nullptr;  // pinned, coherent host memory
@@ -283,10 +351,16 @@ struct AuxStream {
   AuxStream(const AuxStream&) = delete;
   AuxStream& operator=(const AuxStream&) = delete;
   ~AuxStream() { release(); }
-  // Create the stream, events and slot on device `dev` (the current device).
+  // Create what is missing of the stream, events and slot on device `dev` (the
+  // current device).
   void ensure(int dev);
-  // Synchronise the second stream and destroy what ensure() created.
+  // Synchronise the streams and destroy what ensure() (and the owner) created.
   void release();
+  // Destroy the events (ensure() makes new ones).
+  void drop_events();
+  // Take over the streams and the slot of `o`, which has no events; this holds
+  // nothing.
+  void adopt(AuxStream& o);
   // A recorded event is only waited on by calls enqueued right after its
   // record, so a ring much longer than the waits in flight can be reused.
   hipEvent_t record(hipStream_t st) {

@@ -12,6 +12,9 @@
 
 namespace dme {
 
+// device bytes a context keeps idle between solves at most
+constexpr size_t kPoolIdle = (size_t)2 << 30;
+
 // An operator A registered once and kept on the device as A^T, so that served
 // requests name it instead of re-sending n^2 values.
 struct RegisteredOp {
@@ -32,6 +35,7 @@ struct dme_ctx {
   dme::Arena ws;
   dme::DevBuf flags;
   dme::AuxStream aux;  // second stream, event ring and rank slot of the step-level calls
+  std::shared_ptr<dme::DevicePool> pool;  // buffers of its solves
   std::mutex ops_mu;
   std::map<uint64_t, std::shared_ptr<dme::RegisteredOp>> ops;
   uint64_t next_op = 1;

@@ -165,6 +165,8 @@ struct dme_server {
   size_t used = 0, peak = 0;
   uint64_t tick = 0;
   hipStream_t gstream = nullptr, bstream = nullptr;
+  std::vector<hipStream_t> streams;  // idle request streams, at most max_slots
+  std::shared_ptr<dme::DevicePool> mem;  // buffers of the requests' solves and the operator sets
   dme::DevBuf gX, gY, bflags;
   dme::Arena gws;
   std::unique_ptr<dme::Pool> pool;
@@ -273,9 +275,9 @@ CacheEntry& get_operator(dme_server* S, const OpKey& k, int64_t n, bool cold) {
 }
 
 // The request's stream is synchronised first, then its solver goes (which
-// synchronises and destroys the solver's second stream, events and rank slot),
-// and the request's stream last, so nothing of the solve refers to a
-// destroyed stream.
+// synchronises its other streams, destroys its events and hands the streams and
+// its rank slot to the server's pool), and the request's stream last, kept for
+// another request, so nothing of the solve refers to a destroyed stream.
 void release_request_state(dme_server* S, Request& q) {
   for (const OpKey& k : q.keys) {
     auto it = S->cache.find(k);
@@ -283,11 +285,14 @@ void release_request_state(dme_server* S, Request& q) {
   }
   if (q.stream) (void)hipStreamSynchronize(q.stream);
   if (q.sv) {
+    // (a failed tick may have left a grouped product that reads its factor)
+    (void)hipStreamSynchronize(S->gstream);
     q.sv.reset();
     S->used -= q.state_bytes;
   }
-  if (q.stream) {
-    (void)hipStreamDestroy(q.stream);
+  if (q.stream) {  // (synchronised above, and the solver's other streams by the solver)
+    if ((int)S->streams.size() < S->max_slots) S->streams.push_back(q.stream);
+    else (void)hipStreamDestroy(q.stream);
     q.stream = nullptr;
   }
 }
@@ -338,6 +343,10 @@ bool admit(dme_server* S, const std::shared_ptr<Request>& qp) {
       e.users += 1;
       e.last_tick = S->tick;
       sets[k.t] = e.set;
+    }
+    if (!q.stream && !S->streams.empty()) {
+      q.stream = S->streams.back();
+      S->streams.pop_back();
     }
     if (!q.stream) DME_HIP(hipStreamCreateWithFlags(&q.stream, hipStreamNonBlocking));
     q.sv = std::make_unique<Solver>();
@@ -539,6 +548,7 @@ void retire(dme_server* S) {
 void scheduler(dme_server* S) {
   try {
     DME_HIP(hipSetDevice(S->ctx->device));
+    PoolBinding mem(S->mem);
     while (true) {
       {
         std::unique_lock<std::mutex> g(S->mu);
@@ -596,6 +606,7 @@ dme_server* server_start(dme_ctx* ctx, size_t budget, int max_slots) {
   S->max_slots = max_slots;
   DME_HIP(hipStreamCreateWithFlags(&S->gstream, hipStreamNonBlocking));
   DME_HIP(hipStreamCreateWithFlags(&S->bstream, hipStreamNonBlocking));
+  S->mem = std::make_shared<DevicePool>(ctx->device, std::min(kPoolIdle, budget / 4));
   S->bflags.ensure(64);
   DME_HIP(hipMemset(S->bflags.p, 0, 64));
   const int workers = std::max(1, std::min(max_slots, 16));
@@ -741,11 +752,14 @@ void server_stop(dme_server* S) {
     if (q.result) dme_result_free(q.result);
     q.result = nullptr;
     q.sv.reset();
-    if (q.stream) (void)hipStreamDestroy(q.stream);
+    if (q.stream) S->streams.push_back(q.stream);
     q.stream = nullptr;
   }
   S->pool.reset();
   S->cache.clear();
+  S->mem->trim();
+  for (hipStream_t st : S->streams) (void)hipStreamDestroy(st);
+  S->streams.clear();
   if (S->gstream) (void)hipStreamDestroy(S->gstream);
   if (S->bstream) (void)hipStreamDestroy(S->bstream);
   delete S;

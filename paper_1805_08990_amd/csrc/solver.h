@@ -172,6 +172,7 @@ struct Solver {
   DevBuf flags;  // int flags[4]; int64 rank at offset 16
   Arena ws;
   AuxStream aux;  // second stream, event ring and rank slot of this solve
+  std::shared_ptr<DevicePool> mem;  // where its buffers and `aux` came from and go back to
 
   double expm_ms = 0.0, quad_ms = 0.0;
   int64_t rank_quad = 0;

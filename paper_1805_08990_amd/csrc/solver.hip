@@ -155,17 +155,26 @@ Solver::~Solver() {
   // the solve's work on both of its streams ends before its events, rank slot
   // and device buffers go
   (void)hipStreamSynchronize(s);
-  if (s3) {
-    (void)hipStreamSynchronize(s3);
-    (void)hipStreamDestroy(s3);
-  }
+  if (s3) (void)hipStreamSynchronize(s3);
+  if (aux.s2) (void)hipStreamSynchronize(aux.s2);
   if (ey_done) (void)hipEventDestroy(ey_done);
+  aux.s3 = s3;
+  if (mem) mem->give_aux(aux);
   aux.release();
   for (const PendingTiming& t : pending) {
     (void)hipEventDestroy(t.a);
     (void)hipEventDestroy(t.b);
   }
   for (hipEvent_t e : event_pool) (void)hipEventDestroy(e);
+  // every stream that used them is synchronised
+  QuietRelease quiet;
+  for (DevBuf* b : {&AT, &B, &CT, &R, &S, &L[0], &L[1], &D[0], &D[1], &lamT3, &ZT3, &W, &Dhat, &WB, &SL, &Fpre, &EW,
+                    &Tk, &ws3.buf, &flags, &ws.buf})
+    b->release();
+  ELI.clear();
+  Q.clear();
+  ops.clear();
+  lop.reset();
 }
 
 void Solver::check_flags(const char* where) {
@@ -190,6 +199,12 @@ void Solver::setup(const dme_problem& prob, const dme_opts& o, bool dre,
   DME_REQUIRE(o.tol > 0, DME_EINVAL, "tol must be positive");
   DME_REQUIRE(prob.r0 >= 0, DME_EINVAL, "r0 must be >= 0");
   DME_REQUIRE(prob.r0 == 0 || (prob.L0 && prob.D0), DME_EINVAL, "r0 > 0 needs L0 and D0");
+  mem = bound_pool();
+  if (mem && aux.s2 == nullptr) {
+    mem->take_aux(aux);
+    s3 = aux.s3;
+    aux.s3 = nullptr;
+  }
   AuxBinding bind(aux);
   n = prob.n;
   p = prob.p;
@@ -257,6 +272,8 @@ void Solver::setup(const dme_problem& prob, const dme_opts& o, bool dre,
     CT.ensure((size_t)n * p * sizeof(double));
     transpose_f64(s, Cd.as<double>(), p, CT.as<double>(), n, p, n, 1.0);
     DME_HIP(hipStreamSynchronize(s));
+    QuietRelease quiet;
+    Cd.release();
   }
   if (provider == nullptr && prob.A) {
     DevBuf A;
@@ -264,6 +281,8 @@ void Solver::setup(const dme_problem& prob, const dme_opts& o, bool dre,
     AT.ensure((size_t)n * n * sizeof(double));
     transpose_f64(s, A.as<double>(), n, AT.as<double>(), n, n, n, 1.0);
     DME_HIP(hipStreamSynchronize(s));
+    QuietRelease quiet;
+    A.release();
     ATp = AT.as<double>();
   }
   if (prob.M) apply_mass_matrix(prob.M);
@@ -384,6 +403,8 @@ std::shared_ptr<OperatorSet> build_operator_set(hipStream_t s, int64_t n, const 
   op->build_ms = ms;
   (void)hipEventDestroy(a);
   (void)hipEventDestroy(b);
+  QuietRelease quiet;  // (s is synchronised)
+  ews.buf.release();
   return op;
 }
 
@@ -473,6 +494,8 @@ void Solver::build_quadrature(double t) {
     ws.reset();
     leja_apply(s, *lop, *plan, Wd, n, kq, Wd, n, ws);
     DME_HIP(hipStreamSynchronize(s));  // the plan's device coefficients go with it
+    QuietRelease quiet;
+    plan.reset();
   } else {
     // dense node operators e^{s_k A^T}: the products e^{s_k A^T} C^T in FP64,
     // or in DME_MIXED through the split-BF16 product (an FP32 copy of each
@@ -923,6 +946,7 @@ double Solver::err_estimate() {
 
 void Solver::run_stage(size_t i, bool ext_product) {
   AuxBinding bind(aux);
+  PoolBinding pool(mem);
   const Stage& st = seq.at(i);
   const double t = st.frac * opts.h;
   switch (st.sub) {
@@ -936,6 +960,7 @@ void Solver::run_stage(size_t i, bool ext_product) {
 
 void Solver::advance(int64_t nsteps) {
   AuxBinding bind(aux);
+  PoolBinding pool(mem);
   ahead = true;
   try {
     for (int64_t it = 0; it < nsteps; ++it) {

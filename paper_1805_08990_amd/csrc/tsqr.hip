@@ -488,36 +488,57 @@ thread_local AuxStream* g_bound_aux = nullptr;
 }  // namespace
 
 void AuxStream::ensure(int dev) {
-  if (s2 != nullptr) {
-    DME_REQUIRE(dev == device, DME_EINTERNAL, "auxiliary stream used on another device");
-    return;
+  DME_REQUIRE(s2 == nullptr || dev == device, DME_EINTERNAL, "auxiliary stream used on another device");
+  if (s2 != nullptr && !ev.empty()) return;
+  if (s2 == nullptr) {
+    device = dev;
+    DME_HIP(hipStreamCreateWithFlags(&s2, hipStreamNonBlocking));
+    DME_HIP(hipHostMalloc((void**)&slot, sizeof(Slot), hipHostMallocCoherent));
+    slot->value = 0;
+    slot->seq = 0;
+    seq = 0;
   }
-  device = dev;
-  DME_HIP(hipStreamCreateWithFlags(&s2, hipStreamNonBlocking));
   ev.assign(64, nullptr);
   for (hipEvent_t& e : ev) DME_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-  DME_HIP(hipHostMalloc((void**)&slot, sizeof(Slot), hipHostMallocCoherent));
-  slot->value = 0;
-  slot->seq = 0;
-  seq = 0;
   next = 0;
 }
 
-void AuxStream::release() {
-  if (s2 == nullptr) return;
-  int cur = 0;
-  (void)hipGetDevice(&cur);
-  if (cur != device) (void)hipSetDevice(device);
-  (void)hipStreamSynchronize(s2);
+void AuxStream::drop_events() {
   for (hipEvent_t e : ev)
     if (e) (void)hipEventDestroy(e);
   ev.clear();
-  (void)hipStreamDestroy(s2);
+}
+
+void AuxStream::release() {
+  if (s2 == nullptr && s3 == nullptr) return;
+  int cur = 0;
+  (void)hipGetDevice(&cur);
+  if (device >= 0 && cur != device) (void)hipSetDevice(device);
+  if (s3) {
+    (void)hipStreamSynchronize(s3);
+    (void)hipStreamDestroy(s3);
+    s3 = nullptr;
+  }
+  if (s2) (void)hipStreamSynchronize(s2);
+  drop_events();
+  if (s2) (void)hipStreamDestroy(s2);
   s2 = nullptr;
   if (slot) (void)hipHostFree(slot);
   slot = nullptr;
-  if (cur != device) (void)hipSetDevice(cur);
+  if (device >= 0 && cur != device) (void)hipSetDevice(cur);
   device = -1;
+}
+
+void AuxStream::adopt(AuxStream& o) {
+  device = o.device;
+  s2 = o.s2;
+  s3 = o.s3;
+  slot = o.slot;
+  seq = o.seq;
+  o.device = -1;
+  o.s2 = nullptr;
+  o.s3 = nullptr;
+  o.slot = nullptr;
 }
 
 AuxBinding::AuxBinding(AuxStream& a) : prev_(g_bound_aux) { g_bound_aux = &a; }
