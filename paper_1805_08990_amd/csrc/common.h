@@ -248,6 +248,10 @@ __device__ inline double wave_sum_f64(double v) { return swap_sum_f64<32>(half_w
 void gemm_f64(hipStream_t s, char ta, char tb, int64_t M, int64_t N, int64_t K,
               double alpha, const double* A, int64_t lda, const double* B, int64_t ldb,
               double beta, double* C, int64_t ldc, Arena* ws = nullptr);
+// C_z = alpha A_z B_z + beta C_z for z < count, X_z = X + z sx; each as gemm_f64.
+void gemm_f64_batch(hipStream_t s, int64_t count, int64_t M, int64_t N, int64_t K, double alpha, const double* A,
+                    int64_t lda, int64_t sa, const double* B, int64_t ldb, int64_t sb, double beta, double* C,
+                    int64_t ldc, int64_t sc, Arena& ws);
 
 // C = alpha A op(B) + beta C (n x n, inner dimension K) where the result is known
 // to be symmetric (products of commuting symmetric matrices, W P^T of a symmetric
@@ -313,11 +317,12 @@ void finite_check_f64(hipStream_t s, const double* X, int64_t rows, int64_t cols
 struct LuWork;
 // Solve P X = Q in place (Q <- P^-1 Q); P (n x n, ld ldp) is destroyed, Q is
 // n x nrhs (ld ldq).  Returns through *info_dev (device int): 0 ok, j+1 if pivot
-// j is exactly zero.
+// j is exactly zero.  Or several systems of one size, P sp and Q sq entries
+// apart, each solved as it would be alone.
 void lu_solve_f64(hipStream_t s, int64_t n, double* P, int64_t ldp, double* Q, int64_t ldq, int64_t nrhs, Arena& ws,
-                  int* info_dev, bool kept = false);
+                  int* info_dev, bool kept = false, int64_t systems = 1, int64_t sp = 0, int64_t sq = 0);
 size_t lu_solve_workspace(int64_t n);
-size_t lu_solve_workspace(int64_t n, int64_t nrhs);
+size_t lu_solve_workspace(int64_t n, int64_t nrhs, int64_t systems = 1);
 
 // Symmetric positive definite P (spd.hip): out = P^-1 (full), P (lower triangle
 // read, ld even) is destroyed; *info_dev as above for a pivot that is not

@@ -22,6 +22,7 @@
 #include "common.h"
 
 #include <cmath>
+#include <vector>
 
 namespace dme {
 
@@ -60,16 +61,28 @@ void expm_params(double nrm1, int* m, int* s) {
 // fast).  The padding row is carried along and never read.
 int64_t expm_ld(int64_t n) { return n + (n & 1); }
 
-size_t expm_workspace(int64_t n) {
+size_t expm_workspace(int64_t n, int64_t count) {
   const size_t nn = (size_t)expm_ld(n) * n * sizeof(double) + 256;
-  return 7 * nn + (size_t)n * sizeof(double) + 512 + std::max(lu_solve_workspace(n), spd_inverse_workspace(n)) +
+  return (5 + 2 * (size_t)count) * nn + (size_t)(n + 2 * count) * sizeof(double) + 768 +
+         std::max(lu_solve_workspace(n, n, count), spd_inverse_workspace(n)) +
          std::max(gemm_f64_workspace(n, n, n), gemm_sym_workspace(n, n)) + 4096;
 }
 
-// E = e^{tX}; X, E are n x n device matrices (contiguous), E must not alias X.
-void expm_f64(hipStream_t s, int64_t n, const double* X, double t, double* E, Arena& ws, int* m_out,
-              int* s_out, int* info_dev, bool kept) {
-  if (n <= 0) return;
+// The LU of a denominator is a chain of small launches up to n of a few
+// thousand, so the exponentials of a quadrature rule share one: as many as take
+// at most kShared bytes (their numerators, denominators and results).  Seven
+// at n = 1030: 5.5 ms against 7 x 3.1.
+int64_t expm_together(int64_t n, int64_t count) {
+  constexpr size_t kShared = (size_t)512 << 20;
+  const size_t each = 3 * (size_t)expm_ld(n) * n * sizeof(double);
+  return std::max<int64_t>(1, std::min<int64_t>({count, 16, (int64_t)(kShared / std::max<size_t>(each, 1))}));
+}
+
+// E[z] = e^{t[z] X}; X, E[z] are n x n device matrices (contiguous), E[z] must
+// not alias X.  m_out, s_out: of the last one.
+void expm_many_f64(hipStream_t s, int64_t n, const double* X, int64_t count, const double* t, double* const* E,
+                   Arena& ws, int* m_out, int* s_out, int* info_dev, bool kept) {
+  if (n <= 0 || count <= 0) return;
   const int64_t ld = expm_ld(n);
   const size_t nn = (size_t)ld * n;
   double* Y = ws.get<double>(nn);
@@ -77,88 +90,109 @@ void expm_f64(hipStream_t s, int64_t n, const double* X, double t, double* E, Ar
   double* Y4 = ws.get<double>(nn);
   double* Y6 = ws.get<double>(nn);
   double* T1 = ws.get<double>(nn);
-  double* U = ws.get<double>(nn);
-  double* V = ws.get<double>(nn);
+  double* Us = ws.get<double>(count * nn);
+  double* Vs = ws.get<double>(count * nn);
   double* colsum = ws.get<double>(n);
-  double* nrm_dev = ws.get<double>(2);  // the norm; whether tX is not symmetric
+  double* nrm_dev = ws.get<double>(2 * count);  // the norm; whether tX is not symmetric
   const size_t mark = ws.used;
 
-  copy_scaled_f64(s, X, n, Y, ld, n, n, t);
-  norm1_f64(s, Y, n, n, ld, colsum, nrm_dev);
-  asymmetry_f64(s, Y, n, ld, nrm_dev + 1);
-  double head[2] = {0.0, 0.0};
-  DME_HIP(hipMemcpyAsync(head, nrm_dev, sizeof(head), hipMemcpyDeviceToHost, s));
+  for (int64_t z = 0; z < count; ++z) {
+    copy_scaled_f64(s, X, n, Y, ld, n, n, t[z]);
+    norm1_f64(s, Y, n, n, ld, colsum, nrm_dev + 2 * z);
+    asymmetry_f64(s, Y, n, ld, nrm_dev + 2 * z + 1);
+  }
+  std::vector<double> head(2 * count, 0.0);
+  DME_HIP(hipMemcpyAsync(head.data(), nrm_dev, 2 * count * sizeof(double), hipMemcpyDeviceToHost, s));
   DME_HIP(hipStreamSynchronize(s));
-  const double nrm = head[0];
-  const bool sym = head[1] == 0.0 && !kept;
-  DME_REQUIRE(std::isfinite(nrm), DME_ENUMERIC, "expm: operator has non-finite entries");
-  int m = 13, sc = 0;
-  expm_params(nrm, &m, &sc);
-  if (m_out) *m_out = m;
-  if (s_out) *s_out = sc;
-  if (sc > 0) scale_f64(s, Y, (int64_t)nn, std::ldexp(1.0, -sc));
-
-  double b[14];
-  pade_coeffs(m, b);
-  auto mm = [&](const double* P, const double* Q, double beta, double* R) {
+  struct Pending {
+    int64_t z;
+    int sc;
+  };
+  std::vector<Pending> lu;  // those whose quotient is in Us, Vs (in that order)
+  bool sym = false;
+  auto mm = [&](const double* P, const double* Q, double beta, double* R, int64_t ldr) {
     ws.used = mark;
-    const int64_t ldr = R == E ? n : ld;
     if (sym) gemm_sym_f64(s, 'N', n, n, 1.0, P, ld, Q, ld, beta, R, ldr, true, ws);
     else gemm_f64(s, 'N', 'N', n, n, n, 1.0, P, ld, Q, ld, beta, R, ldr, &ws);
   };
-  mm(Y, Y, 0.0, Y2);
-  if (m == 13) {
-    mm(Y2, Y2, 0.0, Y4);
-    mm(Y4, Y2, 0.0, Y6);
-    // U = Y (Y6 (b13 Y6 + b11 Y4 + b9 Y2) + b7 Y6 + b5 Y4 + b3 Y2 + b1 I)
-    lincomb3_f64(s, n, ld, b[13], Y6, b[11], Y4, b[9], Y2, 0.0, T1);
-    lincomb3_f64(s, n, ld, b[7], Y6, b[5], Y4, b[3], Y2, b[1], V);
-    mm(Y6, T1, 1.0, V);
-    mm(Y, V, 0.0, U);
-    // V = Y6 (b12 Y6 + b10 Y4 + b8 Y2) + b6 Y6 + b4 Y4 + b2 Y2 + b0 I
-    lincomb3_f64(s, n, ld, b[12], Y6, b[10], Y4, b[8], Y2, 0.0, T1);
-    lincomb3_f64(s, n, ld, b[6], Y6, b[4], Y4, b[2], Y2, b[0], V);
-    mm(Y6, T1, 1.0, V);
-  } else {
-    // plain even powers Y^2, Y^4 = Y^2 Y^2, Y^6 = Y^4 Y^2, Y^8 = Y^6 Y^2
-    const int h = m / 2;  // highest even power index: Y^{2h}
-    double* P8 = T1;
-    if (h >= 2) mm(Y2, Y2, 0.0, Y4);
-    if (h >= 3) mm(Y4, Y2, 0.0, Y6);
-    if (h >= 4) mm(Y6, Y2, 0.0, P8);
-    // odd = b1 I + b3 Y2 + b5 Y4 + b7 Y6 + b9 Y8 ; even = b0 I + b2 Y2 + ...
-    const double* P[5] = {nullptr, Y2, Y4, Y6, P8};
-    auto coef = [&](int j) { return (j <= m) ? b[j] : 0.0; };
-    // V <- odd part first (stored in V temporarily), then U = Y * odd
-    lincomb3_f64(s, n, ld, coef(3), P[1], h >= 2 ? coef(5) : 0.0, h >= 2 ? P[2] : nullptr,
-                 h >= 3 ? coef(7) : 0.0, h >= 3 ? P[3] : nullptr, coef(1), V);
-    if (h >= 4) lincomb3_f64(s, n, ld, 1.0, V, coef(9), P[4], 0.0, nullptr, 0.0, V);
-    mm(Y, V, 0.0, U);
-    lincomb3_f64(s, n, ld, coef(2), P[1], h >= 2 ? coef(4) : 0.0, h >= 2 ? P[2] : nullptr,
-                 h >= 3 ? coef(6) : 0.0, h >= 3 ? P[3] : nullptr, coef(0), V);
-    if (h >= 4) lincomb3_f64(s, n, ld, 1.0, V, coef(8), P[4], 0.0, nullptr, 0.0, V);
+  // E[z] = (cur)^(2^sc), `other` is scratch
+  auto square = [&](double* cur, double* other, int sc, double* Ez) {
+    for (int q = 0; q < sc; ++q) {
+      const bool last = q == sc - 1;
+      mm(cur, cur, 0.0, last ? Ez : other, last ? n : ld);
+      std::swap(cur, other);
+    }
+    if (sc == 0) copy_f64(s, cur, ld, Ez, n, n, n);
+  };
+
+  for (int64_t z = 0; z < count; ++z) {
+    const double nrm = head[2 * z];
+    sym = head[2 * z + 1] == 0.0 && !kept;
+    double* U = Us + lu.size() * nn;
+    double* V = Vs + lu.size() * nn;
+    DME_REQUIRE(std::isfinite(nrm), DME_ENUMERIC, "expm: operator has non-finite entries");
+    int m = 13, sc = 0;
+    expm_params(nrm, &m, &sc);
+    if (m_out) *m_out = m;
+    if (s_out) *s_out = sc;
+    if (count > 1) copy_scaled_f64(s, X, n, Y, ld, n, n, t[z]);
+    if (sc > 0) scale_f64(s, Y, (int64_t)nn, std::ldexp(1.0, -sc));
+
+    double b[14];
+    pade_coeffs(m, b);
+    mm(Y, Y, 0.0, Y2, ld);
+    if (m == 13) {
+      mm(Y2, Y2, 0.0, Y4, ld);
+      mm(Y4, Y2, 0.0, Y6, ld);
+      // U = Y (Y6 (b13 Y6 + b11 Y4 + b9 Y2) + b7 Y6 + b5 Y4 + b3 Y2 + b1 I)
+      lincomb3_f64(s, n, ld, b[13], Y6, b[11], Y4, b[9], Y2, 0.0, T1);
+      lincomb3_f64(s, n, ld, b[7], Y6, b[5], Y4, b[3], Y2, b[1], V);
+      mm(Y6, T1, 1.0, V, ld);
+      mm(Y, V, 0.0, U, ld);
+      // V = Y6 (b12 Y6 + b10 Y4 + b8 Y2) + b6 Y6 + b4 Y4 + b2 Y2 + b0 I
+      lincomb3_f64(s, n, ld, b[12], Y6, b[10], Y4, b[8], Y2, 0.0, T1);
+      lincomb3_f64(s, n, ld, b[6], Y6, b[4], Y4, b[2], Y2, b[0], V);
+      mm(Y6, T1, 1.0, V, ld);
+    } else {
+      // plain even powers Y^2, Y^4 = Y^2 Y^2, Y^6 = Y^4 Y^2, Y^8 = Y^6 Y^2
+      const int h = m / 2;  // highest even power index: Y^{2h}
+      double* P8 = T1;
+      if (h >= 2) mm(Y2, Y2, 0.0, Y4, ld);
+      if (h >= 3) mm(Y4, Y2, 0.0, Y6, ld);
+      if (h >= 4) mm(Y6, Y2, 0.0, P8, ld);
+      // odd = b1 I + b3 Y2 + b5 Y4 + b7 Y6 + b9 Y8 ; even = b0 I + b2 Y2 + ...
+      const double* P[5] = {nullptr, Y2, Y4, Y6, P8};
+      auto coef = [&](int j) { return (j <= m) ? b[j] : 0.0; };
+      // V <- odd part first (stored in V temporarily), then U = Y * odd
+      lincomb3_f64(s, n, ld, coef(3), P[1], h >= 2 ? coef(5) : 0.0, h >= 2 ? P[2] : nullptr,
+                   h >= 3 ? coef(7) : 0.0, h >= 3 ? P[3] : nullptr, coef(1), V);
+      if (h >= 4) lincomb3_f64(s, n, ld, 1.0, V, coef(9), P[4], 0.0, nullptr, 0.0, V);
+      mm(Y, V, 0.0, U, ld);
+      lincomb3_f64(s, n, ld, coef(2), P[1], h >= 2 ? coef(4) : 0.0, h >= 2 ? P[2] : nullptr,
+                   h >= 3 ? coef(6) : 0.0, h >= 3 ? P[3] : nullptr, coef(0), V);
+      if (h >= 4) lincomb3_f64(s, n, ld, 1.0, V, coef(8), P[4], 0.0, nullptr, 0.0, V);
+    }
+    // U <- V - U (denominator q_m), V <- V + U (numerator p_m); solve q F = p
+    pade_pm_f64(s, U, V, (int64_t)nn);
+    ws.used = mark;
+    if (sym) {
+      spd_inverse_f64(s, n, U, ld, Y6, ld, ws, info_dev);
+      mm(Y6, V, 0.0, T1, ld);
+      square(T1, V, sc, E[z]);
+    } else {
+      lu.push_back({z, sc});
+    }
   }
-  // U <- V - U (denominator q_m), V <- V + U (numerator p_m); solve q F = p
-  pade_pm_f64(s, U, V, (int64_t)nn);
   ws.used = mark;
-  double* cur = V;
-  double* other = T1;
-  if (sym) {
-    spd_inverse_f64(s, n, U, ld, Y6, ld, ws, info_dev);
-    mm(Y6, V, 0.0, T1);
-    std::swap(cur, other);
-  } else {
-    lu_solve_f64(s, n, U, ld, V, ld, n, ws, info_dev, kept);
-  }
-  // squaring phase
-  for (int q = 0; q < sc; ++q) {
-    double* dst = (q == sc - 1) ? E : other;
-    mm(cur, cur, 0.0, dst);
-    if (dst != E) std::swap(cur, other);
-    else cur = E;
-  }
-  if (cur != E) copy_f64(s, cur, ld, E, n, n, n);
+  if (!lu.empty()) lu_solve_f64(s, n, Us, ld, Vs, ld, n, ws, info_dev, kept, (int64_t)lu.size(), (int64_t)nn, (int64_t)nn);
+  sym = false;
+  for (size_t i = 0; i < lu.size(); ++i) square(Vs + i * nn, T1, lu[i].sc, E[lu[i].z]);
   ws.used = mark;
+}
+
+void expm_f64(hipStream_t s, int64_t n, const double* X, double t, double* E, Arena& ws, int* m_out, int* s_out,
+              int* info_dev, bool kept) {
+  expm_many_f64(s, n, X, 1, &t, &E, ws, m_out, s_out, info_dev, kept);
 }
 
 }  // namespace dme

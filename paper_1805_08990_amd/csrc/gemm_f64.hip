@@ -172,12 +172,17 @@ const int hi = lane >> 5, w = (lane >> 1) & (kBK - 1);
 // tiles of the lower triangle only, and entries below the diagonal are also
 // written above it (kSymMirror) or not (kSymLower); kSymLower leaves out rows
 // and columns [skip0, skip1).
+// batch: product z of several (blockIdx.z; K is not split then) has its operands
+// that many entries on.
+struct Batch {
+  int64_t a = 0, b = 0, c = 0;
+};
 constexpr int kSymNone = 0, kSymLower = 1, kSymMirror = 2;
 template <int BM, int BN, bool TA, bool TB, bool VEC, int SYM = kSymNone>
 __global__ __launch_bounds__(kThreads, 2) void gemm_f64_kernel(
     int M, int N, int K, int kchunk, double alpha, const double* __restrict__ A, int64_t lda,
     const double* __restrict__ B, int64_t ldb, double beta, double* __restrict__ C, int64_t ldc,
-    double* __restrict__ partial, int skip0, int skip1) {
+    double* __restrict__ partial, int skip0, int skip1, Batch batch) {
   constexpr int WTM = BM / 2, WTN = BN / 2;  // wave tile
   constexpr int TM = WTM / 16, TN = WTN / 16;
   typedef Slab<TA, BM, VEC> SA;
@@ -198,8 +203,13 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_f64_kernel(
   }
   const int m0 = bi * BM;
   const int n0 = bj * BN;
-  const int kbeg = blockIdx.z * kchunk;
+  const int kbeg = partial ? blockIdx.z * kchunk : 0;
   const int kend = min(K, kbeg + kchunk);
+  if (!partial) {
+    A += blockIdx.z * batch.a;
+    B += blockIdx.z * batch.b;
+    C += blockIdx.z * batch.c;
+  }
   const int r16 = lane & 15;
   const int kq = lane >> 4;
 
@@ -388,13 +398,18 @@ __global__ __launch_bounds__(256) void gemm_f64_small_kernel(int M, int N, int K
                                                              const double* __restrict__ A, int64_t lda,
                                                              const double* __restrict__ B, int64_t ldb,
                                                              double beta, double* __restrict__ C, int64_t ldc,
-                                                             double* __restrict__ partial) {
+                                                             double* __restrict__ partial, Batch batch) {
   __shared__ v4d red[3][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, kq = lane >> 4;
   const int m = blockIdx.x * 16 + r16, n = blockIdx.y * 16 + r16;
   const bool min_ = m < M, nin = n < N;
-  const int kbeg = blockIdx.z * kchunk, kend = min(K, kbeg + kchunk);
+  const int kbeg = partial ? blockIdx.z * kchunk : 0, kend = min(K, kbeg + kchunk);
+  if (!partial) {
+    A += blockIdx.z * batch.a;
+    B += blockIdx.z * batch.b;
+    C += blockIdx.z * batch.c;
+  }
   auto opA = [&](int k) -> double {
     return (min_ && k < kend) ? (TA ? A[k + (int64_t)m * lda] : A[m + (int64_t)k * lda]) : 0.0;
   };
@@ -587,12 +602,14 @@ bool vec_ok(const double* X, int64_t ld, bool kc, int64_t extent) {
 template <int BM, int BN, bool TA, bool TB>
 void launch_tile(hipStream_t s, int M, int N, int K, int nsplit, int kchunk, double alpha,
                  const double* A, int64_t lda, const double* B, int64_t ldb, double beta,
-                 double* C, int64_t ldc, double* partial) {
-  dim3 grid((unsigned)cdiv(M, BM), (unsigned)cdiv(N, BN), (unsigned)nsplit);
+                 double* C, int64_t ldc, double* partial, Batch batch = Batch(), int count = 1) {
+  dim3 grid((unsigned)cdiv(M, BM), (unsigned)cdiv(N, BN), (unsigned)(partial ? nsplit : count));
   // both operands in 16-byte pieces or both in 4-byte ones
-  auto kern = vec_ok(A, lda, TA, M) && vec_ok(B, ldb, !TB, N) ? gemm_f64_kernel<BM, BN, TA, TB, true>
-                                                              : gemm_f64_kernel<BM, BN, TA, TB, false>;
-  hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, M, N, K, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial, 0, 0);
+  auto kern = vec_ok(A, lda, TA, M) && vec_ok(B, ldb, !TB, N) && batch.a % 2 == 0 && batch.b % 2 == 0
+                  ? gemm_f64_kernel<BM, BN, TA, TB, true>
+                  : gemm_f64_kernel<BM, BN, TA, TB, false>;
+  hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, M, N, K, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial, 0, 0,
+                     batch);
 }
 
 template <int BM, int BN>
@@ -930,13 +947,13 @@ void gemm_f64(hipStream_t s, char ta, char tb, int64_t M, int64_t N, int64_t K, 
     const bool TA = (ta == 'T' || ta == 't'), TB = (tb == 'T' || tb == 't');
     const int iM = (int)M, iN = (int)N, iK = (int)K;
     if (!TA && !TB)
-      hipLaunchKernelGGL((gemm_f64_small_kernel<false, false>), grid, dim3(256), 0, s, iM, iN, iK, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
+      hipLaunchKernelGGL((gemm_f64_small_kernel<false, false>), grid, dim3(256), 0, s, iM, iN, iK, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial, Batch());
     else if (TA && !TB)
-      hipLaunchKernelGGL((gemm_f64_small_kernel<true, false>), grid, dim3(256), 0, s, iM, iN, iK, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
+      hipLaunchKernelGGL((gemm_f64_small_kernel<true, false>), grid, dim3(256), 0, s, iM, iN, iK, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial, Batch());
     else if (!TA && TB)
-      hipLaunchKernelGGL((gemm_f64_small_kernel<false, true>), grid, dim3(256), 0, s, iM, iN, iK, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
+      hipLaunchKernelGGL((gemm_f64_small_kernel<false, true>), grid, dim3(256), 0, s, iM, iN, iK, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial, Batch());
     else
-      hipLaunchKernelGGL((gemm_f64_small_kernel<true, true>), grid, dim3(256), 0, s, iM, iN, iK, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial);
+      hipLaunchKernelGGL((gemm_f64_small_kernel<true, true>), grid, dim3(256), 0, s, iM, iN, iK, kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial, Batch());
     DME_HIP(hipGetLastError());
     if (partial) {
       hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)std::min<int64_t>(cdiv(M * N, 256), 4096)), dim3(256),
@@ -970,6 +987,40 @@ void gemm_f64(hipStream_t s, char ta, char tb, int64_t M, int64_t N, int64_t K, 
                        partial, beta, C, ldc);
     DME_HIP(hipGetLastError());
   }
+}
+
+// `count` products of one size, the operands of each sa, sb and sc entries after
+// those of the one before; each is summed as gemm_f64 sums it alone.  One launch
+// where the product alone is one launch of the tiled or the small kernel.
+void gemm_f64_batch(hipStream_t s, int64_t count, int64_t M, int64_t N, int64_t K, double alpha, const double* A,
+                    int64_t lda, int64_t sa, const double* B, int64_t ldb, int64_t sb, double beta, double* C,
+                    int64_t ldc, int64_t sc, Arena& ws) {
+  if (M <= 0 || N <= 0 || count <= 0) return;
+  const Plan p = plan_for(M, N, K);
+  const bool small = M <= kSmallMaxMN && N <= kSmallMaxMN && K <= kSmallMaxK;
+  if (count == 1 || count > 65535 || K <= 0 || use_skinny('N', 'N', M, N, K) || (!small && p.nsplit > 1) ||
+      std::max({M, N, K}) >= (1ll << 31)) {
+    const size_t mark = ws.used;
+    for (int64_t z = 0; z < count; ++z) {
+      ws.used = mark;
+      gemm_f64(s, 'N', 'N', M, N, K, alpha, A + z * sa, lda, B + z * sb, ldb, beta, C + z * sc, ldc, &ws);
+    }
+    return;
+  }
+  const Batch batch{sa, sb, sc};
+  const int iM = (int)M, iN = (int)N, iK = (int)K;
+  double* none = nullptr;
+  if (small)
+    hipLaunchKernelGGL((gemm_f64_small_kernel<false, false>),
+                       dim3((unsigned)cdiv(M, 16), (unsigned)cdiv(N, 16), (unsigned)count), dim3(256), 0, s, iM, iN, iK,
+                       iK, alpha, A, lda, B, ldb, beta, C, ldc, none, batch);
+  else if (p.bm == 128 && p.bn == 128)
+    launch_tile<128, 128, false, false>(s, iM, iN, iK, 1, p.kchunk, alpha, A, lda, B, ldb, beta, C, ldc, none, batch, (int)count);
+  else if (p.bm == 128)
+    launch_tile<128, 64, false, false>(s, iM, iN, iK, 1, p.kchunk, alpha, A, lda, B, ldb, beta, C, ldc, none, batch, (int)count);
+  else
+    launch_tile<64, 64, false, false>(s, iM, iN, iK, 1, p.kchunk, alpha, A, lda, B, ldb, beta, C, ldc, none, batch, (int)count);
+  DME_HIP(hipGetLastError());
 }
 
 // Symmetric results.  128 x 128 tiles where the lower triangle has one for every
@@ -1016,7 +1067,7 @@ void gemm_sym_f64(hipStream_t s, char tb, int64_t n, int64_t K, double alpha, co
   const dim3 grid((unsigned)(nt * (nt + 1) / 2), 1, (unsigned)p.nsplit);
   auto run = [&](auto kern) {
     hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, (int)n, (int)n, (int)K, p.kchunk, alpha, A, lda, B, ldb, beta,
-                       C, ldc, partial, (int)skip0, (int)skip1);
+                       C, ldc, partial, (int)skip0, (int)skip1, Batch());
   };
   if (mirror) {
     DME_REQUIRE(!TB, DME_EINTERNAL, "symmetric product: form not built");

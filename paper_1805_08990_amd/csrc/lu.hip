@@ -45,6 +45,16 @@ struct Moves {
   int src[kPW];
 };
 
+// Several systems of one size at a time: system blockIdx.y has its arrays that
+// many entries after those of the first.  The chain of panels is bound by its
+// latency up to n of a few thousand, so more systems take little more time.
+struct Systems {
+  int64_t a = 0, q = 0;          // matrix, right-hand sides
+  int64_t blk = 0;               // diagonal blocks (and their inverses)
+  int64_t tmp = 0;               // moved block rows
+  int list = 0, mv = 0, lbuf = 0;
+};
+
 // value of lane S of each aligned group of four
 template <int S>
 __device__ inline double quad_bcast_f64(double v) {
@@ -146,7 +156,13 @@ __global__ __launch_bounds__(64) void lu_select_kernel(const double* __restrict_
                                                        int c0, int jb, const int* __restrict__ cand, int ncand,
                                                        int* __restrict__ out, int fin, int o, int jb2,
                                                        double* __restrict__ blk, Moves* __restrict__ mv,
-                                                       double* lbuf, int* __restrict__ info) {
+                                                       double* lbuf, int* __restrict__ info, Systems sys) {
+  A += blockIdx.y * sys.a;
+  if (cand) cand += blockIdx.y * sys.list;
+  out += blockIdx.y * sys.list;
+  blk += blockIdx.y * sys.blk;
+  mv += blockIdx.y * sys.mv;
+  lbuf += blockIdx.y * sys.lbuf;
   __shared__ alignas(16) double srow[kPW][kPW + 2];  // the pivot rows, shifted
   __shared__ double sLU[kPW][kPW + 1], sM[kPW * kPW + kPW];
   __shared__ int spiv[kPW], swho[kPW];
@@ -318,7 +334,10 @@ constexpr int kQuadT = 128;
 template <int O, bool KEPT>
 __global__ __launch_bounds__(kQuadT) void lu_rows_kernel(double* __restrict__ A, int64_t lda, int n, int j0, int jb,
                                                          int jb2, const double* __restrict__ blk,
-                                                         const Moves* __restrict__ mv) {
+                                                         const Moves* __restrict__ mv, Systems sys) {
+  A += blockIdx.y * sys.a;
+  blk += blockIdx.y * sys.blk;
+  mv += blockIdx.y * sys.mv;
   constexpr int LEN = O == 0 ? kNB : kPW, NJ = LEN / 4;
   __shared__ double sM[kPW * LEN + LEN], sR[kPW];
   __shared__ alignas(16) int sdst[kPW], ssrc[kPW];
@@ -401,7 +420,13 @@ __device__ inline void move_rows(double* col, const Moves& mv, int q) {
 __global__ __launch_bounds__(kQuadT) void lu_cols_kernel(double* X, int64_t ldx, int c0, int ncols, double* Q,
                                                          int64_t ldq, int nq, int j0, int jb,
                                                          const double* __restrict__ blk,
-                                                         const Moves* __restrict__ mv, double* __restrict__ tmp) {
+                                                         const Moves* __restrict__ mv, double* __restrict__ tmp,
+                                                         Systems sys) {
+  X += blockIdx.y * sys.a;
+  Q += blockIdx.y * sys.q;
+  blk += blockIdx.y * sys.blk;
+  mv += blockIdx.y * sys.mv;
+  if (tmp) tmp += blockIdx.y * sys.tmp;
   __shared__ double sM[kNB * kNB + kNB];
   __shared__ Moves smv[2];
   const int jb1 = min(jb, kPW), jb2 = jb - jb1;
@@ -467,7 +492,9 @@ __global__ __launch_bounds__(kQuadT) void lu_cols_kernel(double* X, int64_t ldx,
 // Backward substitution with one block's U, a column of Q per quad, as a
 // forward one on the reversed order: Q[j0 .. j0 + jb) <- inv(U11) Q[j0 .. j0 + jb).
 __global__ __launch_bounds__(kQuadT) void lu_back_kernel(double* __restrict__ Q, int64_t ldq, int nq, int j0, int jb,
-                                                         const double* __restrict__ blk) {
+                                                         const double* __restrict__ blk, Systems sys) {
+  Q += blockIdx.y * sys.q;
+  blk += blockIdx.y * sys.blk;
   __shared__ double sM[kNB * kNB + kNB], sR[kNB];
   double st[kNB * kNB / kQuadT];
 #pragma unroll
@@ -508,7 +535,10 @@ __global__ __launch_bounds__(kQuadT) void lu_back_kernel(double* __restrict__ Q,
 
 // Xl = inverse of the block's unit lower triangle (KEPT form): a column of it
 // per quad, by the sums of each entry in ascending order.
-__global__ __launch_bounds__(4 * kNB) void lu_linv_kernel(const double* __restrict__ blk, int jb, double* __restrict__ Xl) {
+__global__ __launch_bounds__(4 * kNB) void lu_linv_kernel(const double* __restrict__ blk, int jb, double* __restrict__ Xl,
+                                                          Systems sys) {
+  blk += blockIdx.y * sys.blk;
+  Xl += blockIdx.y * (int64_t)kNB * kNB;
   __shared__ double sM[kNB * kNB + kNB];
   const int tid = threadIdx.x;
 #pragma unroll
@@ -530,7 +560,10 @@ __global__ __launch_bounds__(4 * kNB) void lu_linv_kernel(const double* __restri
 
 // Xu = inverses of the blocks' upper triangles (KEPT form), one block a
 // workgroup, a column per thread, each entry one dot product in ascending order.
-__global__ __launch_bounds__(kNB) void lu_uinv_kernel(const double* __restrict__ blks, int n, double* __restrict__ Xu) {
+__global__ __launch_bounds__(kNB) void lu_uinv_kernel(const double* __restrict__ blks, int n, double* __restrict__ Xu,
+                                                      Systems sys) {
+  blks += blockIdx.y * sys.blk;
+  Xu += blockIdx.y * sys.blk;
   __shared__ double s[kNB * kNB];
   __shared__ double x[kNB * (kNB + 1)];
   const int b = min(kNB, n - (int)blockIdx.x * kNB);
@@ -553,6 +586,15 @@ __global__ __launch_bounds__(kNB) void lu_uinv_kernel(const double* __restrict__
   for (int idx = threadIdx.x; idx < b * b; idx += kNB) X[idx] = x[idx % b + (idx / b) * (kNB + 1)];
 }
 
+// tmp = the jb rows of Q from j0 on (KEPT form), jb x nq.
+__global__ __launch_bounds__(256) void lu_take_rows_kernel(const double* __restrict__ Q, int64_t ldq, int nq, int jb,
+                                                           double* __restrict__ tmp, Systems sys) {
+  Q += blockIdx.y * sys.q;
+  tmp += blockIdx.y * sys.tmp;
+  const int r = threadIdx.x % kNB, c = blockIdx.x * (256 / kNB) + threadIdx.x / kNB;
+  if (r < jb && c < nq) tmp[r + (int64_t)c * jb] = Q[r + (int64_t)c * ldq];
+}
+
 // players a level of the tournament hands on
 int64_t lu_named(int64_t players) { return cdiv(players, kLeaf) * kPW; }
 
@@ -560,7 +602,7 @@ int64_t lu_named(int64_t players) { return cdiv(players, kLeaf) * kPW; }
 
 size_t lu_solve_workspace(int64_t n) { return lu_solve_workspace(n, n); }
 
-size_t lu_solve_workspace(int64_t n, int64_t nrhs) {
+size_t lu_solve_workspace(int64_t n, int64_t nrhs, int64_t systems) {
   size_t b = 0;
   b += 2 * ((size_t)lu_named(n) * sizeof(int) + 256);                     // tournament lists
   b += (size_t)kPW * kLeaf * sizeof(double);                              // multipliers of a deciding level
@@ -568,22 +610,32 @@ size_t lu_solve_workspace(int64_t n, int64_t nrhs) {
   b += (size_t)(cdiv(n, kNB) + 1) * kNB * kNB * sizeof(double) + 512;     // inverse blocks (kept form)
   b += 2 * sizeof(Moves) + 256;                                           // row moves of a block
   b += (size_t)cdiv(n, kNB) * kNB * kNB * sizeof(double) + 256;           // diagonal blocks
-  b += std::max({gemm_f64_workspace(n, n, kNB), gemm_f64_workspace(n, std::max<int64_t>(nrhs, 1), kNB)}) + 256;
-  return b;
+  return (size_t)systems * b +
+         std::max({gemm_f64_workspace(n, n, kNB), gemm_f64_workspace(n, std::max<int64_t>(nrhs, 1), kNB)}) + 256;
 }
 
 void lu_solve_f64(hipStream_t s, int64_t n, double* A, int64_t lda, double* Q, int64_t ldq, int64_t nrhs, Arena& ws,
-                  int* info_dev, bool kept) {
+                  int* info_dev, bool kept, int64_t systems, int64_t sa, int64_t sq) {
   if (n <= 0) return;
-  DME_REQUIRE(n < (1ll << 30) && nrhs < (1ll << 30), DME_EINVAL, "LU: dimensions too large");
-  int* lists[2] = {ws.get<int>(lu_named(n)), ws.get<int>(lu_named(n))};
-  Moves* mv = ws.get<Moves>(2);
-  double* lbuf = ws.get<double>((size_t)kPW * kLeaf);
-  double* blks = ws.get<double>((size_t)cdiv(n, kNB) * kNB * kNB);
+  DME_REQUIRE(n < (1ll << 30) && nrhs < (1ll << 30) && systems >= 1 && systems < 65536, DME_EINVAL,
+              "LU: dimensions too large");
   const int nq = (int)std::max<int64_t>(nrhs, 0);
-  double* tmp = kept ? ws.get<double>((size_t)kNB * (n + nq)) : nullptr;
-  double* linv = kept ? ws.get<double>((size_t)kNB * kNB) : nullptr;
-  double* uinv = kept ? ws.get<double>((size_t)cdiv(n, kNB) * kNB * kNB) : nullptr;
+  const unsigned nz = (unsigned)systems;
+  Systems sys;
+  sys.a = sa;
+  sys.q = sq;
+  sys.blk = cdiv(n, kNB) * kNB * kNB;
+  sys.tmp = (int64_t)kNB * (n + nq);
+  sys.list = (int)lu_named(n);
+  sys.mv = 2;
+  sys.lbuf = kPW * kLeaf;
+  int* lists[2] = {ws.get<int>((size_t)nz * sys.list), ws.get<int>((size_t)nz * sys.list)};
+  Moves* mv = ws.get<Moves>((size_t)nz * sys.mv);
+  double* lbuf = ws.get<double>((size_t)nz * sys.lbuf);
+  double* blks = ws.get<double>((size_t)nz * sys.blk);
+  double* tmp = kept ? ws.get<double>((size_t)nz * sys.tmp) : nullptr;
+  double* linv = kept ? ws.get<double>((size_t)nz * kNB * kNB) : nullptr;
+  double* uinv = kept ? ws.get<double>((size_t)nz * sys.blk) : nullptr;
   const size_t mark = ws.used;
 
   // pivots of panel o (its rows start at j0 + o) and the factor of its block
@@ -596,13 +648,19 @@ void lu_solve_f64(hipStream_t s, int64_t n, double* A, int64_t lda, double* Q, i
       int* out = lists[lvl & 1];
       // as few rows a lane as keep the level to its number of waves
       auto kern = players <= 64 ? lu_select_kernel<1> : players <= 128 ? lu_select_kernel<2> : lu_select_kernel<3>;
-      hipLaunchKernelGGL(kern, dim3((unsigned)wg), dim3(64), 0, s, A, lda, (int)n, r0, r0, jb, cand, (int)players, out,
-                         wg == 1 ? 1 : 0, o, jb2, blk, mv + (o ? 1 : 0), lbuf, info_dev);
+      hipLaunchKernelGGL(kern, dim3((unsigned)wg, nz), dim3(64), 0, s, A, lda, (int)n, r0, r0, jb, cand, (int)players,
+                         out, wg == 1 ? 1 : 0, o, jb2, blk, mv + (o ? 1 : 0), lbuf, info_dev, sys);
       DME_HIP(hipGetLastError());
       if (wg == 1) return;
       cand = out;
       players = wg * kPW;
     }
+  };
+  // C += alpha X Y (or = for beta 0) of every system
+  auto product = [&](int64_t M, int64_t N, int64_t K, double alpha, const double* X, int64_t ldx, int64_t sx,
+                     const double* Y, int64_t ldy, int64_t sy, double beta, double* C, int64_t ldc, int64_t sc) {
+    ws.used = mark;
+    gemm_f64_batch(s, systems, M, N, K, alpha, X, ldx, sx, Y, ldy, sy, beta, C, ldc, sc, ws);
   };
 
   for (int64_t j0 = 0; j0 < n; j0 += kNB) {
@@ -612,47 +670,42 @@ void lu_solve_f64(hipStream_t s, int64_t n, double* A, int64_t lda, double* Q, i
     select(j0, 0, jb1, jb2, blk);
     const int64_t below1 = n - j0 - jb1;
     if (below1 > 0) {
-      hipLaunchKernelGGL((kept ? lu_rows_kernel<0, true> : lu_rows_kernel<0, false>), dim3((unsigned)cdiv(below1, kQuadT / 4)), dim3(kQuadT), 0, s, A, lda, (int)n,
-                         (int)j0, jb1, jb2, blk, mv);
+      hipLaunchKernelGGL((kept ? lu_rows_kernel<0, true> : lu_rows_kernel<0, false>),
+                         dim3((unsigned)cdiv(below1, kQuadT / 4), nz), dim3(kQuadT), 0, s, A, lda, (int)n, (int)j0, jb1,
+                         jb2, blk, mv, sys);
       DME_HIP(hipGetLastError());
     }
     const int64_t rest = n - j0 - jb;
     if (jb2 > 0) {
       select(j0, kPW, jb2, 0, blk);
       if (rest > 0) {
-        hipLaunchKernelGGL((kept ? lu_rows_kernel<kPW, true> : lu_rows_kernel<kPW, false>), dim3((unsigned)cdiv(rest, kQuadT / 4)), dim3(kQuadT), 0, s, A, lda, (int)n,
-                           (int)j0, jb2, 0, blk, mv + 1);
+        hipLaunchKernelGGL((kept ? lu_rows_kernel<kPW, true> : lu_rows_kernel<kPW, false>),
+                           dim3((unsigned)cdiv(rest, kQuadT / 4), nz), dim3(kQuadT), 0, s, A, lda, (int)n, (int)j0, jb2, 0,
+                           blk, mv + 1, sys);
         DME_HIP(hipGetLastError());
       }
     }
     if (rest + nq > 0) {
-      hipLaunchKernelGGL(lu_cols_kernel, dim3((unsigned)cdiv(rest + nq, kQuadT / 4)), dim3(kQuadT), 0, s, A, lda,
-                         (int)(j0 + jb), (int)rest, Q, ldq, nq, (int)j0, jb, blk, mv, tmp);
+      hipLaunchKernelGGL(lu_cols_kernel, dim3((unsigned)cdiv(rest + nq, kQuadT / 4), nz), dim3(kQuadT), 0, s, A, lda,
+                         (int)(j0 + jb), (int)rest, Q, ldq, nq, (int)j0, jb, blk, mv, tmp, sys);
       DME_HIP(hipGetLastError());
     }
+    double* A12 = A + j0 + (j0 + jb) * lda;
     if (kept && rest + nq > 0) {
-      hipLaunchKernelGGL(lu_linv_kernel, dim3(1), dim3(4 * kNB), 0, s, blk, jb, linv);
+      hipLaunchKernelGGL(lu_linv_kernel, dim3(1, nz), dim3(4 * kNB), 0, s, blk, jb, linv, sys);
       DME_HIP(hipGetLastError());
-      ws.used = mark;
-      if (rest > 0)
-        gemm_f64(s, 'N', 'N', jb, rest, jb, 1.0, linv, jb, tmp, jb, 0.0, A + j0 + (j0 + jb) * lda, lda, &ws);
-      ws.used = mark;
-      if (nq > 0) gemm_f64(s, 'N', 'N', jb, nq, jb, 1.0, linv, jb, tmp + (size_t)jb * rest, jb, 0.0, Q + j0, ldq, &ws);
+      product(jb, rest, jb, 1.0, linv, jb, kNB * kNB, tmp, jb, sys.tmp, 0.0, A12, lda, sa);
+      product(jb, nq, jb, 1.0, linv, jb, kNB * kNB, tmp + (size_t)jb * rest, jb, sys.tmp, 0.0, Q + j0, ldq, sq);
     }
     if (rest > 0) {
       const double* L21 = A + (j0 + jb) + j0 * lda;
-      ws.used = mark;
-      gemm_f64(s, 'N', 'N', rest, rest, jb, -1.0, L21, lda, A + j0 + (j0 + jb) * lda, lda, 1.0,
-               A + (j0 + jb) + (j0 + jb) * lda, lda, &ws);
-      if (nq > 0) {
-        ws.used = mark;
-        gemm_f64(s, 'N', 'N', rest, nq, jb, -1.0, L21, lda, Q + j0, ldq, 1.0, Q + j0 + jb, ldq, &ws);
-      }
+      product(rest, rest, jb, -1.0, L21, lda, sa, A12, lda, sa, 1.0, A + (j0 + jb) * (lda + 1), lda, sa);
+      product(rest, nq, jb, -1.0, L21, lda, sa, Q + j0, ldq, sq, 1.0, Q + j0 + jb, ldq, sq);
     }
   }
   // backward substitution U X = Y
   if (nq > 0 && kept) {
-    hipLaunchKernelGGL(lu_uinv_kernel, dim3((unsigned)cdiv(n, kNB)), dim3(kNB), 0, s, blks, (int)n, uinv);
+    hipLaunchKernelGGL(lu_uinv_kernel, dim3((unsigned)cdiv(n, kNB), nz), dim3(kNB), 0, s, blks, (int)n, uinv, sys);
     DME_HIP(hipGetLastError());
   }
   if (nq > 0)
@@ -660,17 +713,16 @@ void lu_solve_f64(hipStream_t s, int64_t n, double* A, int64_t lda, double* Q, i
       const int64_t j0 = b * kNB;
       const int jb = (int)std::min<int64_t>(kNB, n - j0);
       if (kept) {
-        copy_f64(s, Q + j0, ldq, tmp, jb, jb, nq);
-        ws.used = mark;
-        gemm_f64(s, 'N', 'N', jb, nq, jb, 1.0, uinv + b * kNB * kNB, jb, tmp, jb, 0.0, Q + j0, ldq, &ws);
-      } else
-      hipLaunchKernelGGL(lu_back_kernel, dim3((unsigned)cdiv(nq, kQuadT / 4)), dim3(kQuadT), 0, s, Q, ldq, nq, (int)j0, jb,
-                         blks + b * kNB * kNB);
-      DME_HIP(hipGetLastError());
-      if (j0 > 0) {
-        ws.used = mark;
-        gemm_f64(s, 'N', 'N', j0, nq, jb, -1.0, A + j0 * lda, lda, Q + j0, ldq, 1.0, Q, ldq, &ws);
+        hipLaunchKernelGGL(lu_take_rows_kernel, dim3((unsigned)cdiv(nq, 256 / kNB), nz), dim3(256), 0, s, Q + j0, ldq,
+                           nq, jb, tmp, sys);
+        DME_HIP(hipGetLastError());
+        product(jb, nq, jb, 1.0, uinv + b * kNB * kNB, jb, sys.blk, tmp, jb, sys.tmp, 0.0, Q + j0, ldq, sq);
+      } else {
+        hipLaunchKernelGGL(lu_back_kernel, dim3((unsigned)cdiv(nq, kQuadT / 4), nz), dim3(kQuadT), 0, s, Q, ldq, nq,
+                           (int)j0, jb, blks + b * kNB * kNB, sys);
+        DME_HIP(hipGetLastError());
       }
+      if (j0 > 0) product(j0, nq, jb, -1.0, A + j0 * lda, lda, sa, Q + j0, ldq, sq, 1.0, Q, ldq, sq);
     }
   ws.used = mark;
 }

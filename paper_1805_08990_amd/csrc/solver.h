@@ -15,9 +15,14 @@ namespace dme {
 
 // Host helpers shared by the driver (defined in expm.hip / solver.hip).
 void expm_params(double nrm1, int* m, int* s);
-size_t expm_workspace(int64_t n);
+size_t expm_workspace(int64_t n, int64_t count = 1);
+// how many of `count` exponentials are worth forming at a time
+int64_t expm_together(int64_t n, int64_t count);
 void expm_f64(hipStream_t s, int64_t n, const double* X, double t, double* E, Arena& ws, int* m_out,
               int* s_out, int* info_dev, bool kept = false);
+// several of one X, each as expm_f64 forms it
+void expm_many_f64(hipStream_t s, int64_t n, const double* X, int64_t count, const double* t, double* const* E,
+                   Arena& ws, int* m_out, int* s_out, int* info_dev, bool kept);
 // K-point Gauss-Legendre nodes and weights on [0, t] (ascending nodes).
 void gauss_legendre(int K, double t, std::vector<double>& nodes, std::vector<double>& weights);
 

@@ -367,6 +367,23 @@ size_t operator_set_bytes(int64_t n, int precision, int K, bool keep_nodes) {
   return b;
 }
 
+namespace {
+// Buffers for `count` exponentials at a time, as many as expm_together() says
+// or, where the device has no room for that, one; how many it became.
+template <class Reserve>
+int64_t reserve_expm(int64_t n, int64_t count, Reserve reserve) {
+  const int64_t c = expm_together(n, count);
+  try {
+    reserve(c);
+    return c;
+  } catch (const Error& e) {
+    if (c == 1 || e.code != DME_ENOMEM) throw;
+  }
+  reserve(1);
+  return 1;
+}
+}  // namespace
+
 std::shared_ptr<OperatorSet> build_operator_set(hipStream_t s, int64_t n, const double* AT, double t,
                                                 int precision, int K, bool keep_nodes, int* info_dev) {
   hipEvent_t a, b;
@@ -378,23 +395,27 @@ std::shared_ptr<OperatorSet> build_operator_set(hipStream_t s, int64_t n, const 
   op->t = t;
   op->precision = precision;
   op->K = keep_nodes ? K : 0;
+  const size_t nn = (size_t)n * n * sizeof(double);
+  std::vector<double> times, weights;  // t, then the nodes
+  if (keep_nodes) gauss_legendre(K, t, times, weights);
+  times.insert(times.begin(), t);
+  op->E.ensure(nn);
+  std::vector<double*> to{op->E.as<double>()};
+  op->nodes.resize(op->K);
+  for (DevBuf& b : op->nodes) {
+    b.ensure(nn);
+    to.push_back(b.as<double>());
+  }
   Arena ews;
-  ews.reserve(expm_workspace(n));
-  op->E.ensure((size_t)n * n * sizeof(double));
-  expm_f64(s, n, AT, t, op->E.as<double>(), ews, nullptr, nullptr, info_dev, precision == DME_MIXED);
+  const int64_t each = reserve_expm(n, (int64_t)times.size(), [&](int64_t c) { ews.reserve(expm_workspace(n, c)); });
+  for (size_t q = 0; q < times.size(); q += each) {
+    ews.reset();
+    expm_many_f64(s, n, AT, std::min<int64_t>(each, times.size() - q), &times[q], &to[q], ews, nullptr, nullptr, info_dev,
+                  precision == DME_MIXED);
+  }
   if (precision == DME_MIXED) {
     op->mix = mixed_op_new();
     mixed_op_build(s, n, op->E.as<double>(), *op->mix);
-  }
-  if (keep_nodes) {
-    std::vector<double> nodes, weights;
-    gauss_legendre(K, t, nodes, weights);
-    op->nodes.resize(K);
-    for (int q = 0; q < K; ++q) {
-      ews.reset();
-      op->nodes[q].ensure((size_t)n * n * sizeof(double));
-      expm_f64(s, n, AT, nodes[q], op->nodes[q].as<double>(), ews, nullptr, nullptr, info_dev, precision == DME_MIXED);
-    }
   }
   DME_HIP(hipEventRecord(b, s));
   DME_HIP(hipEventSynchronize(b));
@@ -534,13 +555,19 @@ void Solver::build_quadrature(double t) {
       for (int q = 0; q < K; ++q) node_product(op.nodes[q].as<double>(), q);
     } else {
       DME_REQUIRE(ATp != nullptr, DME_EINTERNAL, "quadrature factor needs the operator or its nodes");
-      DevBuf Ek((size_t)n * n * sizeof(double));
+      DevBuf Ek;
       Arena ews;
-      ews.reserve(expm_workspace(n));
-      for (int q = 0; q < K; ++q) {
+      const int64_t each = reserve_expm(n, K, [&](int64_t c) {
+        Ek.ensure((size_t)c * n * n * sizeof(double));
+        ews.reserve(expm_workspace(n, c));
+      });
+      std::vector<double*> to(each);
+      for (int64_t z = 0; z < each; ++z) to[z] = Ek.as<double>() + z * n * n;
+      for (int64_t q = 0; q < K; q += each) {
+        const int64_t c = std::min<int64_t>(each, K - q);
         ews.reset();
-        expm_f64(s, n, ATp, nodes[q], Ek.as<double>(), ews, nullptr, nullptr, flag_dev() + 1, kept());
-        node_product(Ek.as<double>(), q);
+        expm_many_f64(s, n, ATp, c, &nodes[q], to.data(), ews, nullptr, nullptr, flag_dev() + 1, kept());
+        for (int64_t z = 0; z < c; ++z) node_product(to[z], (int)(q + z));
       }
     }
   }
