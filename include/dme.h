@@ -163,8 +163,9 @@ int dme_solver_create(dme_ctx *ctx, const dme_problem *prob, const dme_opts *opt
 int dme_solver_step(dme_solver *sv, int64_t nsteps);
 /* steps taken, total steps N, current rank r. */
 int dme_solver_state(const dme_solver *sv, int64_t *step, int64_t *nsteps_total, int64_t *rank);
-/* Setup timing (ms): e^{tA^T} formation, quadrature factor; rank of the
- * quadrature factor. */
+/* Setup timing (ms): e^{tA^T} formation (with the quadrature nodes' exponentials
+ * where all are formed at a time), quadrature factor; rank of the quadrature
+ * factor. */
 int dme_solver_setup_info(const dme_solver *sv, double *expm_ms, double *quad_ms, int64_t *rank_quad);
 int dme_solver_result(dme_solver *sv, dme_result **out);
 

@@ -341,8 +341,10 @@ void Solver::setup(const dme_problem& prob, const dme_opts& o, bool dre,
           set->plan = leja_plan(*lop, {t}, 1);
           ops[t] = set;
         } else {
+          // (with the quadrature's node exponentials where all are formed at a time)
+          const bool nodes = st.sub == Sub::T12 && !lop && expm_together(n, opts.quad_nodes + 1) > opts.quad_nodes;
           ops[t] = provider ? (*provider)(t)
-                            : build_operator_set(s, n, ATp, t, opts.precision, 0, false, flag_dev() + 1);
+                            : build_operator_set(s, n, ATp, t, opts.precision, opts.quad_nodes, nodes, flag_dev() + 1);
         }
         DME_REQUIRE(ops[t] && ops[t]->n == n && ops[t]->precision == opts.precision, DME_EINTERNAL,
                     "operator set does not match the problem");
@@ -353,6 +355,10 @@ void Solver::setup(const dme_problem& prob, const dme_opts& o, bool dre,
       EventTimer tm(s);
       build_quadrature(t);
       quad_ms += tm.stop_ms();
+      if (!provider) {
+        QuietRelease quiet;  // (done with, and s synchronised, before the factor was compressed)
+        ops[t]->nodes.clear();
+      }
     }
   }
   check_flags("setup");
