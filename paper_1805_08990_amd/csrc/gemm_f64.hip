@@ -173,9 +173,11 @@ const int hi = lane >> 5, w = (lane >> 1) & (kBK - 1);
 // written above it (kSymMirror) or not (kSymLower); kSymLower leaves out rows
 // and columns [skip0, skip1).
 // batch: product z of several (blockIdx.z; K is not split then) has its operands
-// that many entries on.
+// that many entries on.  tail >= 0 (SYM, BM = 64): the 64 x 64 quarters of the
+// 128 x 128 tiles from number `tail` on.
 struct Batch {
   int64_t a = 0, b = 0, c = 0;
+  int tail = -1;
 };
 constexpr int kSymNone = 0, kSymLower = 1, kSymMirror = 2;
 template <int BM, int BN, bool TA, bool TB, bool VEC, int SYM = kSymNone>
@@ -195,11 +197,17 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_f64_kernel(
   const int wm = wave & 1, wn = wave >> 1;
   int bi = blockIdx.x, bj = blockIdx.y;
   if (SYM) {  // tile bi (bi + 1) / 2 + bj, bj <= bi
-    const int t = blockIdx.x;
+    const bool quarters = BM == 64 && batch.tail >= 0;
+    const int t = quarters ? batch.tail + (int)blockIdx.x / 4 : (int)blockIdx.x;
     bi = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
     while (bi * (bi + 1) / 2 > t) --bi;
     while ((bi + 1) * (bi + 2) / 2 <= t) ++bi;
     bj = t - bi * (bi + 1) / 2;
+    if (quarters) {
+      bi = 2 * bi + (blockIdx.x & 1);
+      bj = 2 * bj + ((blockIdx.x >> 1) & 1);
+      if (bj > bi || bi * BM >= M) return;  // (uniform)
+    }
   }
   const int m0 = bi * BM;
   const int n0 = bj * BN;
@@ -1063,22 +1071,31 @@ void gemm_sym_f64(hipStream_t s, char tb, int64_t n, int64_t K, double alpha, co
   const SymPlan p = sym_plan(n, K, mirror);
   const size_t mark = ws.used;
   double* partial = p.nsplit > 1 ? ws.get<double>((size_t)p.nsplit * n * n) : nullptr;
-  const int64_t nt = cdiv(n, p.bm);
-  const dim3 grid((unsigned)(nt * (nt + 1) / 2), 1, (unsigned)p.nsplit);
-  auto run = [&](auto kern) {
-    hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, (int)n, (int)n, (int)K, p.kchunk, alpha, A, lda, B, ldb, beta,
-                       C, ldc, partial, (int)skip0, (int)skip1, Batch());
+  const int64_t nt = cdiv(n, p.bm), tiles = nt * (nt + 1) / 2;
+  // A long K and few tiles more than fill the chip two to a CU: those few would
+  // take as long again as a whole round (n = 4096: 16 of 528 tiles, 1.53 ms in
+  // place of 1.05), so they go as quarters, on four times the CUs.
+  const int64_t slots = 2 * kMinTiles;
+  const int64_t few = (p.bm == 128 && p.nsplit == 1 && K >= 1024 && tiles > slots && tiles % slots <= kMinTiles / 2)
+                          ? tiles % slots : 0;
+  auto run = [&](auto kern, int64_t blocks, Batch batch) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks, 1, (unsigned)p.nsplit), dim3(kThreads), 0, s, (int)n, (int)n, (int)K,
+                       p.kchunk, alpha, A, lda, B, ldb, beta, C, ldc, partial, (int)skip0, (int)skip1, batch);
+    DME_HIP(hipGetLastError());
   };
+  Batch tail;
+  tail.tail = (int)(tiles - few);
   if (mirror) {
     DME_REQUIRE(!TB, DME_EINTERNAL, "symmetric product: form not built");
-    if (p.bm == 128) run(gemm_f64_kernel<128, 128, false, false, true, kSymMirror>);
-    else run(gemm_f64_kernel<64, 64, false, false, true, kSymMirror>);
+    if (p.bm == 128) run(gemm_f64_kernel<128, 128, false, false, true, kSymMirror>, tiles - few, Batch());
+    else run(gemm_f64_kernel<64, 64, false, false, true, kSymMirror>, tiles, Batch());
+    if (few) run(gemm_f64_kernel<64, 64, false, false, true, kSymMirror>, 4 * few, tail);
   } else {
     DME_REQUIRE(TB, DME_EINTERNAL, "symmetric product: form not built");
-    if (p.bm == 128) run(gemm_f64_kernel<128, 128, false, true, true, kSymLower>);
-    else run(gemm_f64_kernel<64, 64, false, true, true, kSymLower>);
+    if (p.bm == 128) run(gemm_f64_kernel<128, 128, false, true, true, kSymLower>, tiles - few, Batch());
+    else run(gemm_f64_kernel<64, 64, false, true, true, kSymLower>, tiles, Batch());
+    if (few) run(gemm_f64_kernel<64, 64, false, true, true, kSymLower>, 4 * few, tail);
   }
-  DME_HIP(hipGetLastError());
   if (partial) {
     hipLaunchKernelGGL(splitk_reduce_sym_kernel, dim3((unsigned)cdiv(n, 256), (unsigned)n), dim3(256), 0, s, (int)n,
                        p.nsplit, alpha, partial, beta, C, ldc);

@@ -5,6 +5,7 @@ dimension), and node times whose exponentials take different degrees and numbers
 of squarings."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import workloads as wl
@@ -27,3 +28,23 @@ def test_node_exponentials(ctx, n, size):
     Lo, Do, _ = oracle.solve(A, C, steps * h, h, kind="dle", tol=1e-12)
     assert k == steps
     assert oracle.lowrank_rel_err(L, D, Lo, Do) < 1e-10
+
+
+# a few tiles more than whole rounds of the chip (32 to 35 tiles of 128 a side),
+# the last one whole, ragged at either quarter, and a single row
+@pytest.mark.parametrize("n", [4096, 4033, 4000, 4097, 4421])
+def test_symmetric_products_with_few_tiles_left(ctx, n):
+    """e^X of the 1D Laplacian, whose eigenvectors are sines."""
+    announce("symmetric tail", n)
+    i = torch.arange(1, n + 1, dtype=torch.float64, device="cuda")
+    S = np.sqrt(2.0 / (n + 1)) * torch.sin(np.pi / (n + 1) * (i[:, None] * i[None, :] % (2 * (n + 1))))
+    lam = -3.0 * (2.0 - 2.0 * torch.cos(np.pi / (n + 1) * i))  # ||X||_1 = 12: [13/13], two squarings
+    X = torch.zeros((n, n), dtype=torch.float64, device="cuda")
+    X.diagonal().fill_(-6.0)
+    X.diagonal(1).fill_(3.0)
+    X.diagonal(-1).fill_(3.0)
+    E, m, s = ctx.expm(X, 1.0)
+    assert (m, s) == (13, 2)
+    ref = (S * torch.exp(lam)) @ S
+    assert float(torch.linalg.norm(E - ref) / torch.linalg.norm(ref)) < 1e-12
+    assert torch.equal(E, E.t())
