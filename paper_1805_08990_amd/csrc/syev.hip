@@ -1591,6 +1591,93 @@ __global__ __launch_bounds__(256) void polar_gemm_kernel(int k, int ncol, const 
   }
 }
 
+// All steps for k <= 64 by one workgroup of sixteen waves, a 16 x 16 tile of each
+// product a wave, Z and B in LDS: six launches of 2.6 us with as long between
+// them become one of 6 (a DLE solve at n = 256, a chain of short kernels,
+// 13.9 -> 11.6 ms).  Every entry is summed as the kernels above sum it
+// (four partial sums over the steps 4 w + 16 s of the inner dimension, added in
+// wave order), so the result does not depend on which of the two ran.
+constexpr int kPolarOneK = 64;
+__global__ __launch_bounds__(1024) void polar_one_kernel(int k, int ncol, const double* __restrict__ Zin,
+                                                         const int* __restrict__ cl_of, const int* __restrict__ clusters,
+                                                         int* cl_fail, double* __restrict__ Zout) {
+  constexpr int N = kPolarOneK, LD = N + 4;
+  __shared__ double z[2][N * LD];  // Z, column by column; entries past k and ncol are zero
+  __shared__ double b[N * LD];     // B
+  __shared__ int scl[N], sfail[N];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r16 = lane & 15, kq = lane >> 4;
+  const int m0 = (wave & 3) * 16, n0 = (wave >> 2) * 16;
+  double st[N * N / 1024];
+#pragma unroll
+  for (int u = 0; u < N * N / 1024; ++u) {
+    const int e = tid + 1024 * u, i = e % N, c = e / N;
+    st[u] = Zin[min(i, k - 1) + (int64_t)min(c, ncol - 1) * k];
+  }
+#pragma unroll
+  for (int u = 0; u < N * N / 1024; ++u) {
+    const int e = tid + 1024 * u, i = e % N, c = e / N;
+    double v = st[u];
+    pin(v);
+    z[0][i + c * LD] = i < k && c < ncol ? v : 0.0;
+  }
+  if (tid < N) {
+    scl[tid] = tid < ncol ? cl_of[tid] : -1;
+    sfail[tid] = 0;
+  }
+  __syncthreads();
+  // the 16 x 16 tile of op(X) Y at (m0, n0), inner dimension K; x(m, q), y(q, n)
+  auto product = [&](int K, auto x, auto y) {
+    pv4d acc[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) acc[w] = pv4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < N / 16; ++s)
+      if (16 * s < K) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const int q = 4 * w + 16 * s + kq;
+          acc[w] = __builtin_amdgcn_mfma_f64_16x16x4f64(y(q, n0 + r16), x(m0 + r16, q), acc[w], 0, 0, 0);
+        }
+      }
+    return ((acc[0] + acc[1]) + acc[2]) + acc[3];
+  };
+  int cur = 0;
+  for (int step = 0; step < kPolarSteps; ++step) {
+    const double* Z = z[cur];
+    if (m0 < ncol && n0 < ncol) {  // (uniform over the wave)
+      const pv4d g = product(k, [&](int m, int q) { return Z[q + m * LD]; }, [&](int q, int n) { return Z[q + n * LD]; });
+      const int m = m0 + r16, cm = scl[m];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int n = n0 + v * 4 + kq;
+        const double dl = m == n ? 1.0 : 0.0;
+        const bool mine = cm >= 0 && scl[n] == cm;
+        if (step == 0 && mine && !(fabs(g[v] - dl) * clusters[2 * cm + 1] < kPolarTol)) sfail[cm % N] = 1;
+        b[m + n * LD] = mine ? dl + 0.5 * (dl - g[v]) : dl;
+      }
+    }
+    __syncthreads();
+    if (m0 < k && n0 < ncol) {
+      const int n = n0 + r16;
+      const bool live = scl[n] >= 0 && !sfail[scl[n] >= 0 ? scl[n] % N : 0];
+      const pv4d o = product(
+          ncol, [&](int m, int q) { return Z[m + q * LD]; },
+          [&](int q, int nn) { return nn >= ncol || q >= ncol ? 0.0 : live ? b[q + nn * LD] : q == nn ? 1.0 : 0.0; });
+#pragma unroll
+      for (int v = 0; v < 4; ++v) z[cur ^ 1][m0 + r16 + (n0 + v * 4 + kq) * LD] = o[v];
+    }
+    __syncthreads();
+    cur ^= 1;
+  }
+#pragma unroll
+  for (int u = 0; u < N * N / 1024; ++u) {
+    const int e = tid + 1024 * u, i = e % N, c = e / N;
+    if (i < k && c < ncol) Zout[i + (int64_t)c * k] = z[cur][i + c * LD];
+  }
+  if (tid < ncol && scl[tid] >= 0 && sfail[scl[tid] % N]) cl_fail[scl[tid]] = 1;
+}
+
 // Orthonormalise the vectors of one cluster (blockIdx.x), in ascending
 // eigenvalue order, by right-looking modified Gram-Schmidt done twice: at
 // step j every later vector loses its component along z_j.  The later vectors
@@ -1998,7 +2085,12 @@ void syev_trunc_f64(hipStream_t s, int64_t k, const double* M, int64_t ldm, doub
     double* Z1 = ws.get<double>((size_t)k * nc);
     double* Zo = Z1;  // Zf -> Zo each step
     const dim3 gg((unsigned)cdiv(nc, 16), (unsigned)cdiv(nc, 16)), ga((unsigned)cdiv(k, 16), (unsigned)cdiv(nc, 16));
-    for (int step = 0; step < kPolarSteps; ++step) {
+    if (k <= kPolarOneK) {
+      hipLaunchKernelGGL(polar_one_kernel, dim3(1), dim3(1024), 0, s, ki, nc, Zt, cl_of, clusters, cl_fail, Z1);
+      DME_HIP(hipGetLastError());
+      Zf = Z1;
+    }
+    for (int step = 0; step < kPolarSteps && k > kPolarOneK; ++step) {
       hipLaunchKernelGGL(polar_gemm_kernel<kPolarGram>, gg, dim3(256), 0, s, ki, nc, Zf, (const double*)nullptr,
                          cl_of, clusters, cl_fail, step == 0, G);
       DME_HIP(hipGetLastError());
