@@ -309,6 +309,10 @@ void copy_scaled_f64(hipStream_t s, const double* X, int64_t ldx, double* Y, int
 size_t diff_norms_workspace();
 void diff_norms_f64(hipStream_t s, const double* A, int64_t lda, const double* B, int64_t ldb,
                     int64_t rows, int64_t cols, double* part, double* out);
+// W = [L1 (n x r), L2 (n x p)] (null: those columns stay) and
+// Dhat = blkdiag(D1, scale2 (D2 or I)), all contiguous.
+void assemble_f64(hipStream_t s, int64_t n, const double* L1, int64_t r, const double* L2, int64_t p, double* W,
+                  const double* D1, const double* D2, double scale2, double* Dhat);
 // NaN/Inf scan: sets *flag = 1 if any entry of X is not finite.
 void finite_check_f64(hipStream_t s, const double* X, int64_t rows, int64_t cols, int64_t ld,
                       int* flag);

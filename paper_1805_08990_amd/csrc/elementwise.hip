@@ -131,6 +131,38 @@ __global__ void blkdiag2_kernel(const double* D1, int64_t k1, int64_t ld1, const
   }
 }
 
+// A compression's input in one launch: the columns [L1 (r), L2 (p)] of W (L1 or
+// L2 null: those columns stay) and Dhat = blkdiag(D1, scale2 (D2 or I)).  Block
+// row y is a column of W, then one of Dhat; 1024 rows a block.  (Copied part by
+// part this was three launches of 2 us in a chain of fifteen.)
+__global__ __launch_bounds__(kT) void assemble_kernel(int64_t n, const double* __restrict__ L1, int r,
+                                                      const double* __restrict__ L2, int p, double* __restrict__ W,
+                                                      const double* __restrict__ D1, const double* __restrict__ D2,
+                                                      double scale2, double* __restrict__ Dhat) {
+  const int k = r + p, y = blockIdx.y;
+  if (y < k) {
+    const double* from = y < r ? (L1 ? L1 + (int64_t)y * n : nullptr) : (L2 ? L2 + (int64_t)(y - r) * n : nullptr);
+    if (from == nullptr) return;
+    double* to = W + (int64_t)y * n;
+#pragma unroll
+    for (int u = 0; u < 1024 / kT; ++u) {
+      const int64_t i = blockIdx.x * 1024 + u * kT + threadIdx.x;
+      if (i < n) to[i] = from[i];
+    }
+    return;
+  }
+  const int c = y - k;
+#pragma unroll
+  for (int u = 0; u < 1024 / kT; ++u) {
+    const int i = blockIdx.x * 1024 + u * kT + threadIdx.x;
+    if (i >= k) continue;
+    double v = 0.0;
+    if (i < r && c < r) v = D1[i + (int64_t)c * r];
+    else if (i >= r && c >= r) v = D2 ? scale2 * D2[i - r + (int64_t)(c - r) * p] : (i == c ? scale2 : 0.0);
+    Dhat[i + (int64_t)c * k] = v;
+  }
+}
+
 __global__ void finite_kernel(const double* X, int64_t rows, int64_t cols, int64_t ld, int* flag) {
   const int64_t total = rows * cols;
   bool bad = false;
@@ -262,6 +294,16 @@ void blkdiag2_f64(hipStream_t s, const double* D1, int64_t k1, int64_t ld1, cons
   if (k <= 0) return;
   hipLaunchKernelGGL(blkdiag2_kernel, dim3(grid_for(k * k)), dim3(kT), 0, s, D1, k1, ld1, D2, k2,
                      ld2, scale2, out, ldo);
+  DME_HIP(hipGetLastError());
+}
+
+void assemble_f64(hipStream_t s, int64_t n, const double* L1, int64_t r, const double* L2, int64_t p, double* W,
+                  const double* D1, const double* D2, double scale2, double* Dhat) {
+  const int64_t k = r + p;
+  if (k <= 0) return;
+  DME_REQUIRE(2 * k < 65536, DME_EINVAL, "compression input too wide");
+  hipLaunchKernelGGL(assemble_kernel, dim3((unsigned)cdiv(std::max(n, k), 1024), (unsigned)(2 * k)), dim3(kT), 0, s, n, L1,
+                     (int)r, L2, (int)p, W, D1, D2, scale2, Dhat);
   DME_HIP(hipGetLastError());
 }
 

@@ -16,7 +16,7 @@
 // function of it, so symmetric: its products then take half the work
 // (gemm_sym_f64), and step 4 is F = (V - U)^-1 (V + U) with the inverse of the
 // positive definite denominator (spd.hip).  Measured at n = 4096 with four
-// squarings: 20.0 ms against 36.2 for the general path.  A caller that depends
+// squarings: 16.9 ms against 36.2 for the general path.  A caller that depends
 // on the last bit of E (kept; see Solver::kept) takes full products and the LU
 // in its kept form instead.
 #include "common.h"
@@ -70,8 +70,8 @@ size_t expm_workspace(int64_t n, int64_t count) {
 
 // The LU of a denominator is a chain of small launches up to n of a few
 // thousand, so the exponentials of a quadrature rule share one: as many as take
-// at most kShared bytes (their numerators, denominators and results).  Seven
-// at n = 1030: 5.5 ms against 7 x 3.1.
+// at most kShared bytes (their numerators, denominators and results).  A
+// solve at n = 1030 with seven nodes, all of it: 14.2 ms against 31.3.
 int64_t expm_together(int64_t n, int64_t count) {
   constexpr size_t kShared = (size_t)512 << 20;
   const size_t each = 3 * (size_t)expm_ld(n) * n * sizeof(double);

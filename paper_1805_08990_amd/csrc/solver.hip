@@ -15,6 +15,7 @@
 #include "solver.h"
 
 #include <cmath>
+#include <utility>
 
 namespace dme {
 
@@ -817,7 +818,7 @@ void Solver::apply_T1(double t) {
   if (r == 0) return;
   apply_E(t, Lc(), r, Ln(), n);
   ++nprod;
-  copy_f64(s, Dc(), r, Dn(), r, r, r);
+  std::swap(D[0], D[1]);  // D stays as it is
   cur ^= 1;
 }
 
@@ -825,10 +826,8 @@ void Solver::apply_T2(double t) {
   settle_beside();
   drop_ahead();
   double* Wd = W.as<double>();
-  if (r > 0) copy_f64(s, Lc(), n, Wd, n, n, r);
-  copy_f64(s, CT.as<double>(), n, Wd + r * n, n, n, p);
   const int64_t k = r + p;
-  blkdiag2_f64(s, Dc(), r, r, nullptr, p, 1, t, Dhat.as<double>(), k);
+  assemble_f64(s, n, Lc(), r, CT.as<double>(), p, Wd, Dc(), nullptr, t, Dhat.as<double>());
   compress_into(k);
 }
 
@@ -851,8 +850,8 @@ void Solver::apply_T12(double t, bool ext_product) {
   if (k > 0) {
     AuxStream& ax = aux_stream();
     DME_HIP(hipStreamWaitEvent(ax.s2, ax.record(s), 0));
-    blkdiag2_f64(ax.s2, Dc(), r, r, f.D.as<double>(), f.r, f.r, 1.0, Dhat.as<double>(), k);
-    if (f.r > 0 && !from_ahead) copy_f64(ax.s2, f.L.as<double>(), n, Wd + r * n, n, n, f.r);
+    assemble_f64(ax.s2, n, nullptr, r, from_ahead ? nullptr : f.L.as<double>(), f.r, Wd, Dc(), f.D.as<double>(), 1.0,
+                 Dhat.as<double>());
     if (d_lowrank && Fpre.bytes > 0) {
       const LowRankD lr{lamT3.as<double>(), ZT3.as<double>(), t3, r, m, 1};
       double* F = Fpre.as<double>();

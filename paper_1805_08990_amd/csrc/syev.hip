@@ -24,7 +24,8 @@
 //                         three Newton-Schulz steps Z <- Z (3I - Z^T Z) / 2
 //                         (restricted to each cluster's block), two MFMA
 //                         products a step: Z^T Z (the first one also checks
-//                         the clusters) and Z B with B formed as it is read;
+//                         the clusters) and Z B with B formed as it is read
+//                         (k <= 64: all of it in one launch);
 //      orth_kernel      : one workgroup per remaining cluster orthonormalises
 //                         its vectors (right-looking modified Gram-Schmidt,
 //                         two passes).
