@@ -365,6 +365,12 @@ __device__ __forceinline__ void tridiag_phase(const double* Min, int64_t ldm, do
       }
     }
   };
+  // the last lanes' entries past the tile's rows: no wave writes them, and the
+  // sums over whole vectors take them times the reflector's zeros, which holds
+  // for numbers only (what an earlier workgroup left there need not be one)
+  if constexpr (KM < 64 * NC2) {
+    if (t < 64 * NC2 - KM) pb[KM + t] = cb[KM + t] = 0.0;
+  }
   if (c == 0) {  // column 0 (every half-wave its rows)
 #pragma unroll
     for (int u = 0; u < RT; ++u) cb[rbase + u] = a[u][0];
