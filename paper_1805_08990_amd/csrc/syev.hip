@@ -1864,15 +1864,18 @@ __global__ __launch_bounds__(64 * kBtCols) void form_q_kernel(const double* __re
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int c = blockIdx.x * kBtCols + wv;
   const int jtop = min(k - 3, (int)blockIdx.x * kBtCols + kBtCols - 2);
-  double z[NS], st[kPer][NS], tst = 0.0;
+  double z[NS], st[kPer][NS], ts[kPer], tst = 0.0;
 #pragma unroll
   for (int s = 0; s < NS; ++s) z[s] = (lane + 64 * s == c) ? 1.0 : 0.0;
   // the chunk of reflectors jlo .. jlo + kBtChunk - 1, at clamped addresses; the
-  // unit entries and the zeros (above them, past k, past jtop) come with store()
+  // unit entries and the zeros (above them, past k, past jtop, and where tau = 0:
+  // the reduction leaves that column's place unwritten) come with store()
   auto load = [&](int jlo) {
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
-      const double* col = A + (int64_t)min(jlo + wv + kBtCols * q, k - 1) * lda;
+      const int j = min(jlo + wv + kBtCols * q, k - 1);
+      const double* col = A + (int64_t)j * lda;
+      ts[q] = tau[j];
 #pragma unroll
       for (int s = 0; s < NS; ++s) st[q][s] = col[min(lane + 64 * s, k - 1)];
     }
@@ -1887,7 +1890,7 @@ __global__ __launch_bounds__(64 * kBtCols) void form_q_kernel(const double* __re
         const int i = lane + 64 * s;
         double v = st[q][s];
         pin(v);
-        v = (i > j + 1 && i < k && j <= jtop) ? v : 0.0;
+        v = (i > j + 1 && i < k && j <= jtop && ts[q] != 0.0) ? v : 0.0;
         vb[wv + kBtCols * q][i] = (i == j + 1) ? 1.0 : v;
       }
     }
