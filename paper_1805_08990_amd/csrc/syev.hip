@@ -1391,7 +1391,8 @@ __global__ __launch_bounds__(128) void twist_kernel(const double* __restrict__ d
     }
   }
   __syncthreads();  // both parts of gamma are in LDS
-  // twist r = argmin |gamma_i| (lowest i among equals), by wave 1
+  // twist r = argmin |gamma_i| (lowest i among equals), by wave 1; row 0 where no
+  // gamma is finite (a reduction that overflowed), so that r is always a row
   if (w == 1) {
     double best = DBL_MAX;
     int bi = 0x7fffffff;
@@ -1406,7 +1407,7 @@ __global__ __launch_bounds__(128) void twist_kernel(const double* __restrict__ d
       const int oi = __shfl_xor(bi, off, 64);
       if (ob < best || (ob == best && oi < bi)) { best = ob; bi = oi; }
     }
-    if (lane == 0) rsh = bi;
+    if (lane == 0) rsh = bi < k ? bi : 0;
   }
   __syncthreads();
   const int r = rsh;
