@@ -18,9 +18,10 @@
 //   cols   : the remaining columns and the right-hand sides: both panels' row
 //            moves and U12 = inv(L11) A12.
 //   A22    : A22 - L21 U12 and the same of the right-hand sides (FP64 MFMA).
-// The kept form rounds every entry as the method's first implementation did (a
-// division per multiplier, block triangles applied through their inverses by
-// products), for callers whose results depend on the last bit (expm.hip).
+// The kept form rounds every entry as the method's first implementation did with
+// the same pivots (a division per multiplier, block triangles applied through
+// their inverses by products), for callers whose results depend on the last bit
+// (Solver::kept).
 // What bounds it: up to n of a few thousand the chain of panels (a launch pair
 // per column takes 18 us a column; at n = 4096 a 64-column block of this takes
 // 180 us and the whole solve 17 ms instead of 95); beyond that the trailing

@@ -132,8 +132,11 @@ struct Solver {
   int64_t r = 0;
   // DME_MIXED: the split-BF16 products turn a difference in the last bit of what
   // they are given into one of 1e-9 within a few steps, so such a solve keeps
-  // every rounding of the operators, the quadrature factor and the compressions
-  // as it has always been, and its results stay the same to the bit
+  // every rounding of the mass matrix's solve, the operators, the quadrature
+  // factor and the compressions as it has always been.  Its results are then the
+  // same to the bit while the LU's pivots are: always up to 192 rows, where the
+  // tournament is partial pivoting, and beyond that for a matrix in which it
+  // names the same rows
   bool kept() const { return opts.precision == DME_MIXED; }
   bool d_diag = true;  // D is diagonal (a compression's output; T3 fills it)
   // D = diag(lamT3) - t3 Z Z^T with Z in ZT3 (T3 applied to a diagonal D)

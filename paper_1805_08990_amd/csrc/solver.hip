@@ -497,7 +497,7 @@ void Solver::apply_mass_matrix(const double* Mh) {
   }
   Arena lws;
   lws.reserve(lu_solve_workspace(n, nr));
-  lu_solve_f64(s, n, Mt.as<double>(), n, rhs.as<double>(), n, nr, lws, flag_dev() + 1);
+  lu_solve_f64(s, n, Mt.as<double>(), n, rhs.as<double>(), n, nr, lws, flag_dev() + 1, kept());
   copy_f64(s, rhs.as<double>(), n, AT.as<double>(), n, n, n);
   copy_f64(s, rhs.as<double>() + (size_t)n * n, n, CT.as<double>(), n, n, p);
   DME_HIP(hipStreamSynchronize(s));
