@@ -135,7 +135,10 @@ typedef struct {
 /* ------------------------------------------------------------- context */
 /* Create a context on HIP device `device`.  `stream` is the hipStream_t the
  * context enqueues on (NULL: the null stream); it stays owned by the caller
- * and must outlive the context. */
+ * and must outlive the context.  A finished solve leaves its device buffers to
+ * the context's next ones: up to 2 GiB stay allocated between solves, and are
+ * freed when the context and its solvers go or when an allocation of the library
+ * fails (another allocator in the process does not see them as free). */
 int dme_create(dme_ctx **ctx, int device, void *stream);
 void dme_destroy(dme_ctx *ctx);
 const char *dme_strerror(int code);
@@ -292,7 +295,8 @@ int dme_syev(dme_ctx *ctx, int64_t k, const double *M, double tol, int64_t max_k
 /* A request server on a context: solves submitted as they arrive run with
  * continuous batching.  A scheduler thread admits waiting requests in
  * arrival order whenever a slot is free and the device-memory ledger
- * (cached operators + per-solve state) stays within the budget, advances all
+ * (cached operators + per-solve state + the buffers that these leave for the
+ * next, freed when the room is needed) stays within the budget, advances all
  * admitted solves one time step per tick (solves that share an operator
  * e^{tA^T} get one product over their concatenated factors; compressions and
  * Riccati updates of different solves overlap on their own streams), and
@@ -318,7 +322,10 @@ typedef struct {
  * submissions.  The registration lives as long as the context.             */
 int dme_register_operator(dme_ctx *ctx, const double *A, int64_t n, uint64_t *op_id);
 /* Start a server on ctx with a device-memory budget (bytes) for cached
- * operators and solve state, and at most max_slots solves admitted at once. */
+ * operators, solve state and buffers kept for reuse, and at most max_slots
+ * solves admitted at once.  The workspace of an operator that is being built is
+ * beside the budget where the budget has no room for it, as are the blocks of a
+ * grouped product. */
 int dme_server_start(dme_ctx *ctx, size_t hbm_budget_bytes, int max_slots, dme_server **srv);
 /* Build and cache the operator set of op_id for step fraction t (e^{tA^T},
  * its FP32 copy in DME_MIXED, and the quad_nodes Gauss-Legendre node

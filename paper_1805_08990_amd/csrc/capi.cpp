@@ -14,14 +14,22 @@ thread_local std::string g_last_error;
 
 void fail(int code, const std::string& msg) { throw Error{code, msg}; }
 
+namespace {
+thread_local std::shared_ptr<DevicePool> g_pool;
+thread_local bool g_exact = false;
+thread_local int g_quiet = 0;
+}  // namespace
+
 void DevBuf::alloc(size_t b) {
   if (b == 0) b = 256;
   pool = bound_pool();
+  spare = 0;
   if (pool) {
     b = (b + 4095) & ~size_t(4095);
     size_t got = b;
-    if ((p = pool->take(&got)) != nullptr) {
+    if ((p = pool->take(&got, g_exact)) != nullptr) {
       bytes = got;
+      spare = got - b;
       return;
     }
   }
@@ -40,16 +48,11 @@ void DevBuf::alloc(size_t b) {
   bytes = b;
 }
 
-namespace {
-thread_local std::shared_ptr<DevicePool> g_pool;
-thread_local int g_quiet = 0;
-}  // namespace
-
 void DevBuf::release() {
   if (p && own) {
     if (pool) {
       if (g_quiet == 0) pool->wait();
-      pool->give(p, bytes);
+      pool->give(p, bytes, spare);
     } else {
       (void)hipFree(p);
     }
@@ -57,11 +60,19 @@ void DevBuf::release() {
   pool.reset();
   p = nullptr;
   bytes = 0;
+  spare = 0;
   own = true;
 }
 
-PoolBinding::PoolBinding(const std::shared_ptr<DevicePool>& pool) : prev_(std::move(g_pool)) { g_pool = pool; }
-PoolBinding::~PoolBinding() { g_pool = std::move(prev_); }
+PoolBinding::PoolBinding(std::shared_ptr<DevicePool> pool, bool exact)
+    : prev_(std::move(g_pool)), prev_exact_(g_exact) {
+  g_pool = std::move(pool);
+  g_exact = exact;
+}
+PoolBinding::~PoolBinding() {
+  g_pool = std::move(prev_);
+  g_exact = prev_exact_;
+}
 const std::shared_ptr<DevicePool>& bound_pool() { return g_pool; }
 QuietRelease::QuietRelease() { ++g_quiet; }
 QuietRelease::~QuietRelease() { --g_quiet; }
@@ -105,20 +116,23 @@ void DevicePool::wait() const {
   if (cur != device_) (void)hipSetDevice(cur);
 }
 
-void* DevicePool::take(size_t* bytes) {
+void* DevicePool::take(size_t* bytes, bool exact) {
   std::lock_guard<std::mutex> g(mu_);
   auto it = blocks_.lower_bound(*bytes);
-  if (it == blocks_.end() || it->first > *bytes + *bytes / 4 + (64u << 10)) return nullptr;
+  const size_t over = exact ? 0 : *bytes / 4 + (64u << 10);
+  if (it == blocks_.end() || it->first > *bytes + over) return nullptr;
   void* p = it->second;
+  spare_ += it->first - *bytes;
   *bytes = it->first;
   idle_ -= it->first;
   blocks_.erase(it);
   return p;
 }
 
-void DevicePool::give(void* p, size_t bytes) {
+void DevicePool::give(void* p, size_t bytes, size_t spare) {
   {
     std::lock_guard<std::mutex> g(mu_);
+    spare_ -= spare;
     if (idle_ + bytes <= max_idle_) try {
         blocks_.emplace(bytes, p);
         idle_ += bytes;
@@ -127,6 +141,11 @@ void DevicePool::give(void* p, size_t bytes) {
       }
   }
   (void)hipFree(p);
+}
+
+size_t DevicePool::unused() const {
+  std::lock_guard<std::mutex> g(mu_);
+  return idle_ + spare_;
 }
 
 void DevicePool::trim() {

@@ -47,9 +47,10 @@ struct AuxStream;
 // often a page table update each to allocate, and hipFree waits for the whole
 // device (4 of the 36 ms of a DRE solve at n = 1024, 7 of 24 of a GDRE solve at
 // n = 2025, 3 of the 18 a served request takes).  A block is handed out again only for a
-// request of nearly its size.  Idle blocks are bounded by max_idle bytes; what
-// goes beyond is freed, and all of it when the pool goes or any allocation of
-// the library fails.  Safe to use from several threads.
+// request of nearly its size (at most a quarter less; of its very size for an
+// exact binding).  Idle blocks are bounded by max_idle bytes; what goes beyond is
+// freed, and all of it when the pool goes or any allocation of the library fails.
+// Safe to use from several threads.
 //
 // Work that used a block has to be over when it is given back, whatever stream
 // it ran on: DevBuf::release() waits for the device as hipFree does, unless
@@ -62,8 +63,11 @@ class DevicePool {
   DevicePool(const DevicePool&) = delete;
   DevicePool& operator=(const DevicePool&) = delete;
   // an idle block of at least *bytes (its size in *bytes), or null
-  void* take(size_t* bytes);
-  void give(void* p, size_t bytes);
+  void* take(size_t* bytes, bool exact);
+  // spare: how much larger than asked for the block was when it was taken
+  void give(void* p, size_t bytes, size_t spare);
+  // bytes of the idle blocks, and what handed out ones have beyond the request
+  size_t unused() const;
   void trim();  // free every idle block and stream set
   static void trim_all();  // ... of every pool of the process
   void wait() const;       // for all work on the pool's device
@@ -75,21 +79,23 @@ class DevicePool {
 
  private:
   int device_;
-  size_t max_idle_, idle_ = 0;
-  std::mutex mu_;
+  size_t max_idle_, idle_ = 0, spare_ = 0;
+  mutable std::mutex mu_;
   std::multimap<size_t, void*> blocks_;
   std::vector<std::unique_ptr<AuxStream>> aux_;
 };
-// Buffers the calling thread allocates come from `pool` while this lives.
+// Buffers the calling thread allocates come from `pool` while this lives (exact:
+// only blocks of their very size).
 class PoolBinding {
  public:
-  explicit PoolBinding(const std::shared_ptr<DevicePool>& pool);
+  explicit PoolBinding(std::shared_ptr<DevicePool> pool, bool exact = false);
   ~PoolBinding();
   PoolBinding(const PoolBinding&) = delete;
   PoolBinding& operator=(const PoolBinding&) = delete;
 
  private:
   std::shared_ptr<DevicePool> prev_;
+  bool prev_exact_;
 };
 const std::shared_ptr<DevicePool>& bound_pool();
 // The calling thread's releases need no wait: the streams whose work used the
@@ -106,20 +112,21 @@ struct QuietRelease {
 struct DevBuf {
   void* p = nullptr;
   size_t bytes = 0;
+  size_t spare = 0;  // of a pool's block, beyond the request
   bool own = true;
   std::shared_ptr<DevicePool> pool;
   DevBuf() = default;
   explicit DevBuf(size_t b) { alloc(b); }
   DevBuf(const DevBuf&) = delete;
   DevBuf& operator=(const DevBuf&) = delete;
-  DevBuf(DevBuf&& o) noexcept : p(o.p), bytes(o.bytes), own(o.own), pool(std::move(o.pool)) {
-    o.p = nullptr; o.bytes = 0; o.own = true;
+  DevBuf(DevBuf&& o) noexcept : p(o.p), bytes(o.bytes), spare(o.spare), own(o.own), pool(std::move(o.pool)) {
+    o.p = nullptr; o.bytes = 0; o.spare = 0; o.own = true;
   }
   DevBuf& operator=(DevBuf&& o) noexcept {
     if (this != &o) {
       release();
-      p = o.p; bytes = o.bytes; own = o.own; pool = std::move(o.pool);
-      o.p = nullptr; o.bytes = 0; o.own = true;
+      p = o.p; bytes = o.bytes; spare = o.spare; own = o.own; pool = std::move(o.pool);
+      o.p = nullptr; o.bytes = 0; o.spare = 0; o.own = true;
     }
     return *this;
   }

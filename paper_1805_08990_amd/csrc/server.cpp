@@ -3,7 +3,8 @@
 // Clients submit solves (host data copied on submit) against operators
 // registered once on the context.  A scheduler thread runs "ticks": it admits
 // waiting requests in arrival order while a slot is free and the HBM ledger
-// (operator cache + per-solve state) stays within the budget, then advances
+// (operator cache + per-solve state + the blocks these left idle for the next)
+// stays within the budget, then advances
 // every admitted solve by one time step, and retires the finished ones.
 //
 // Inside a tick the stages of the step sequences run in lockstep.  For a T12
@@ -234,8 +235,21 @@ size_t admission_bytes(dme_server* S, const Request& q) {
   return b;
 }
 
+// What the server holds of the budget: cached operator sets and solve state, the
+// blocks they have left idle, and what a reused block of a solve has beyond its
+// request (operator sets take blocks of their own size only).
+size_t held(dme_server* S) { return S->used + S->mem->unused(); }
+
+// The idle blocks go where they and `need` more bytes are over the budget.
+void settle(dme_server* S, size_t need) {
+  if (held(S) + need > S->budget) S->mem->trim();
+  S->peak = std::max(S->peak, held(S));
+}
+
 // Drop cached operator sets no admitted solve uses, least recently used
-// first, until `need` more bytes fit.  Returns whether they fit.
+// first, until `need` more bytes fit beside what is in use, then idle blocks.
+// Returns whether they fit (with no solve admitted nothing in use has more than
+// its request, so what is within the budget fits).
 bool make_room(dme_server* S, size_t need) {
   while (S->used + need > S->budget) {
     auto victim = S->cache.end();
@@ -246,10 +260,14 @@ bool make_room(dme_server* S, size_t need) {
     S->used -= victim->second.bytes;
     S->cache.erase(victim);
   }
-  return true;
+  settle(S, need);
+  return S->active.empty() || held(S) + need <= S->budget;
 }
 
-CacheEntry& get_operator(dme_server* S, const OpKey& k, int64_t n, bool cold) {
+// `later`: bytes that will be added to the ledger after this set.  The set's
+// exponentials are formed together as far as the rest of the budget holds the
+// workspace (one alone may go past it while it is formed).
+CacheEntry& get_operator(dme_server* S, const OpKey& k, int64_t n, bool cold, size_t later) {
   auto it = S->cache.find(k);
   if (it != S->cache.end()) return it->second;
   std::shared_ptr<RegisteredOp> op = find_op(S->ctx, k.op);
@@ -258,14 +276,16 @@ CacheEntry& get_operator(dme_server* S, const OpKey& k, int64_t n, bool cold) {
   const double t0 = now_s();
   CacheEntry e;
   const bool nodes = !op->lop;
+  e.bytes = operator_set_bytes(n, k.precision, k.K, nodes);
+  const size_t kept = held(S) + e.bytes + later;
+  PoolBinding exact(bound_pool(), true);
   e.set = build_operator_set(S->bstream, n, op->AT.as<double>(), k.t, k.precision, k.K, nodes,
-                             S->bflags.as<int>());
+                             S->bflags.as<int>(), S->budget > kept ? S->budget - kept : 0);
   int info = 0;
   DME_HIP(hipMemcpy(&info, S->bflags.as<int>(), sizeof(int), hipMemcpyDeviceToHost));
   DME_REQUIRE(info == 0, DME_ENUMERIC, "operator: singular Pade denominator");
-  e.bytes = operator_set_bytes(n, k.precision, k.K, nodes);
   S->used += e.bytes;
-  S->peak = std::max(S->peak, S->used);
+  settle(S, later);
   if (cold) {
     std::lock_guard<std::mutex> g(S->mu);
     S->cold_builds += 1;
@@ -289,6 +309,7 @@ void release_request_state(dme_server* S, Request& q) {
     (void)hipStreamSynchronize(S->gstream);
     q.sv.reset();
     S->used -= q.state_bytes;
+    settle(S, 0);
   }
   if (q.stream) {  // (synchronised above, and the solver's other streams by the solver)
     if ((int)S->streams.size() < S->max_slots) S->streams.push_back(q.stream);
@@ -338,8 +359,10 @@ bool admit(dme_server* S, const std::shared_ptr<Request>& qp) {
   if (!fits) return false;
   try {
     std::map<double, std::shared_ptr<OperatorSet>> sets;
+    size_t later = need;
     for (const OpKey& k : q.keys) {
-      CacheEntry& e = get_operator(S, k, q.n, true);
+      if (!S->cache.count(k)) later -= operator_set_bytes(q.n, k.precision, k.K, keeps_nodes(S, k.op));
+      CacheEntry& e = get_operator(S, k, q.n, true, later);
       e.users += 1;
       e.last_tick = S->tick;
       sets[k.t] = e.set;
@@ -359,7 +382,6 @@ bool admit(dme_server* S, const std::shared_ptr<Request>& qp) {
       q.sv->lop = op->lop;
     }
     S->used += q.state_bytes;
-    S->peak = std::max(S->peak, S->used);
     dme_problem prob{};
     prob.n = q.n;
     prob.m = q.is_dre ? q.m : 0;
@@ -376,6 +398,7 @@ bool admit(dme_server* S, const std::shared_ptr<Request>& qp) {
     o.precision = q.precision;
     OperatorProvider provider = [&sets](double t) { return sets.at(t); };
     q.sv->setup(prob, o, q.is_dre != 0, &provider);
+    settle(S, 0);
     q.status = kActive;
     if (q.t_admit < 0) q.t_admit = now_s();
     S->active.push_back(qp);
@@ -429,6 +452,7 @@ void grouped_product(dme_server* S, const OperatorSet& set, std::vector<Request*
     DME_HIP(hipEventRecord(ev, q->stream));
     DME_HIP(hipStreamWaitEvent(S->gstream, ev, 0));
   }
+  PoolBinding exact(S->mem, true);
   S->gX.ensure((size_t)n * cols * sizeof(double));
   S->gY.ensure((size_t)n * cols * sizeof(double));
   double* X = S->gX.as<double>();
@@ -631,7 +655,7 @@ void server_warm(dme_server* S, uint64_t op_id, double t, int precision, int K) 
   if (S->cache.count(k)) return;
   const size_t b = operator_set_bytes(op->n, precision, k.K, !op->lop);
   DME_REQUIRE(make_room(S, b), DME_ENOMEM, "operator does not fit the server budget");
-  CacheEntry& e = get_operator(S, k, op->n, false);
+  CacheEntry& e = get_operator(S, k, op->n, false, 0);
   e.last_tick = S->tick;
 }
 

@@ -63,9 +63,12 @@ struct OperatorSet {
 // Device bytes an operator set holds.
 size_t operator_set_bytes(int64_t n, int precision, int K, bool keep_nodes);
 // Form the operator set of AT = A^T (device, n x n) on stream s (synchronous).
-// info_dev: device int receiving a nonzero LU pivot failure flag.
+// info_dev: device int receiving a nonzero LU pivot failure flag.  Its
+// exponentials are formed as many at a time as `scratch` bytes of workspace
+// allow, one at least.
 std::shared_ptr<OperatorSet> build_operator_set(hipStream_t s, int64_t n, const double* AT, double t,
-                                                int precision, int K, bool keep_nodes, int* info_dev);
+                                                int precision, int K, bool keep_nodes, int* info_dev,
+                                                size_t scratch = SIZE_MAX);
 
 // Supplies the operator set for a step fraction t (a cache shared by
 // several solves); null means the solve builds its own.

@@ -376,10 +376,12 @@ size_t operator_set_bytes(int64_t n, int precision, int K, bool keep_nodes) {
 
 namespace {
 // Buffers for `count` exponentials at a time, as many as expm_together() says
-// or, where the device has no room for that, one; how many it became.
+// and `scratch` bytes hold or, where the device has no room for that, one; how
+// many it became.
 template <class Reserve>
-int64_t reserve_expm(int64_t n, int64_t count, Reserve reserve) {
-  const int64_t c = expm_together(n, count);
+int64_t reserve_expm(int64_t n, int64_t count, size_t scratch, Reserve reserve) {
+  int64_t c = expm_together(n, count);
+  while (c > 1 && expm_workspace(n, c) > scratch) --c;
   try {
     reserve(c);
     return c;
@@ -392,7 +394,8 @@ int64_t reserve_expm(int64_t n, int64_t count, Reserve reserve) {
 }  // namespace
 
 std::shared_ptr<OperatorSet> build_operator_set(hipStream_t s, int64_t n, const double* AT, double t,
-                                                int precision, int K, bool keep_nodes, int* info_dev) {
+                                                int precision, int K, bool keep_nodes, int* info_dev,
+                                                size_t scratch) {
   hipEvent_t a, b;
   DME_HIP(hipEventCreate(&a));
   DME_HIP(hipEventCreate(&b));
@@ -414,7 +417,8 @@ std::shared_ptr<OperatorSet> build_operator_set(hipStream_t s, int64_t n, const 
     to.push_back(b.as<double>());
   }
   Arena ews;
-  const int64_t each = reserve_expm(n, (int64_t)times.size(), [&](int64_t c) { ews.reserve(expm_workspace(n, c)); });
+  const int64_t each =
+      reserve_expm(n, (int64_t)times.size(), scratch, [&](int64_t c) { ews.reserve(expm_workspace(n, c)); });
   for (size_t q = 0; q < times.size(); q += each) {
     ews.reset();
     expm_many_f64(s, n, AT, std::min<int64_t>(each, times.size() - q), &times[q], &to[q], ews, nullptr, nullptr, info_dev,
@@ -564,7 +568,7 @@ void Solver::build_quadrature(double t) {
       DME_REQUIRE(ATp != nullptr, DME_EINTERNAL, "quadrature factor needs the operator or its nodes");
       DevBuf Ek;
       Arena ews;
-      const int64_t each = reserve_expm(n, K, [&](int64_t c) {
+      const int64_t each = reserve_expm(n, K, SIZE_MAX, [&](int64_t c) {
         Ek.ensure((size_t)c * n * n * sizeof(double));
         ews.reserve(expm_workspace(n, c));
       });
