@@ -268,6 +268,9 @@ struct Solver {
   // multiple of kRowBlock, or n; 0: none) and their split
   void plan_beside(int64_t k, int64_t* rows, int* ns) const;
   void apply_E(double t, const double* X, int64_t r, double* Y, int64_t ldy);
+  // e^{tA^T} of the solve's own A, with the quadrature nodes' exponentials beside
+  // it (nodes) where the device has room for them
+  std::shared_ptr<OperatorSet> own_operator_set(double t, bool nodes);
   void build_quadrature(double t);
   void apply_mass_matrix(const double* M);
 };

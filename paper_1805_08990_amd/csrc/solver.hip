@@ -344,8 +344,7 @@ void Solver::setup(const dme_problem& prob, const dme_opts& o, bool dre,
         } else {
           // (with the quadrature's node exponentials where all are formed at a time)
           const bool nodes = st.sub == Sub::T12 && !lop && expm_together(n, opts.quad_nodes + 1) > opts.quad_nodes;
-          ops[t] = provider ? (*provider)(t)
-                            : build_operator_set(s, n, ATp, t, opts.precision, opts.quad_nodes, nodes, flag_dev() + 1);
+          ops[t] = provider ? (*provider)(t) : own_operator_set(t, nodes);
         }
         DME_REQUIRE(ops[t] && ops[t]->n == n && ops[t]->precision == opts.precision, DME_EINTERNAL,
                     "operator set does not match the problem");
@@ -364,6 +363,18 @@ void Solver::setup(const dme_problem& prob, const dme_opts& o, bool dre,
   }
   check_flags("setup");
   step = 0;
+}
+
+std::shared_ptr<OperatorSet> Solver::own_operator_set(double t, bool nodes) {
+  auto build = [&](bool with) {
+    return build_operator_set(s, n, ATp, t, opts.precision, opts.quad_nodes, with, flag_dev() + 1);
+  };
+  if (nodes) try {
+      return build(true);
+    } catch (const Error& e) {  // no room: build_quadrature() forms the nodes, one by one if need be
+      if (e.code != DME_ENOMEM) throw;
+    }
+  return build(false);
 }
 
 size_t operator_set_bytes(int64_t n, int precision, int K, bool keep_nodes) {
@@ -396,10 +407,7 @@ int64_t reserve_expm(int64_t n, int64_t count, size_t scratch, Reserve reserve) 
 std::shared_ptr<OperatorSet> build_operator_set(hipStream_t s, int64_t n, const double* AT, double t,
                                                 int precision, int K, bool keep_nodes, int* info_dev,
                                                 size_t scratch) {
-  hipEvent_t a, b;
-  DME_HIP(hipEventCreate(&a));
-  DME_HIP(hipEventCreate(&b));
-  DME_HIP(hipEventRecord(a, s));
+  EventTimer tm(s);
   auto op = std::make_shared<OperatorSet>();
   op->n = n;
   op->t = t;
@@ -428,13 +436,7 @@ std::shared_ptr<OperatorSet> build_operator_set(hipStream_t s, int64_t n, const 
     op->mix = mixed_op_new();
     mixed_op_build(s, n, op->E.as<double>(), *op->mix);
   }
-  DME_HIP(hipEventRecord(b, s));
-  DME_HIP(hipEventSynchronize(b));
-  float ms = 0.f;
-  DME_HIP(hipEventElapsedTime(&ms, a, b));
-  op->build_ms = ms;
-  (void)hipEventDestroy(a);
-  (void)hipEventDestroy(b);
+  op->build_ms = tm.stop_ms();
   QuietRelease quiet;  // (s is synchronised)
   ews.buf.release();
   return op;
@@ -569,6 +571,7 @@ void Solver::build_quadrature(double t) {
       DevBuf Ek;
       Arena ews;
       const int64_t each = reserve_expm(n, K, SIZE_MAX, [&](int64_t c) {
+        Ek.release();  // (what a first try that found no room got)
         Ek.ensure((size_t)c * n * n * sizeof(double));
         ews.reserve(expm_workspace(n, c));
       });
