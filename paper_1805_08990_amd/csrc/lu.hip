@@ -165,7 +165,7 @@ __global__ __launch_bounds__(64) void lu_select_kernel(const double* __restrict_
   mv += blockIdx.y * sys.mv;
   lbuf += blockIdx.y * sys.lbuf;
   __shared__ alignas(16) double srow[kPW][kPW + 2];  // the pivot rows, shifted
-  __shared__ double sLU[kPW][kPW + 1], sM[kPW * kPW + kPW];
+  __shared__ double sM[kPW * kPW + kPW];
   __shared__ int spiv[kPW], swho[kPW];
   const int lane = threadIdx.x;
   int row[R];
@@ -268,7 +268,6 @@ __global__ __launch_bounds__(64) void lu_select_kernel(const double* __restrict_
 #pragma unroll
   for (int u = 0; u < kEach; ++u) {
     const int e = lane + u * 64, i = e % kPW, c = e / kPW;
-    sLU[i][c] = w[u];
     sM[e] = c < i ? w[u] : 0.0;
     // a column past jb of a narrow panel is not part of the factor
     if (i < jb && c < jb) blk[o + i + (o + c) * kNB] = w[u];
