@@ -60,8 +60,9 @@ typedef struct dme_solver dme_solver;
  * Mass-matrix form (Sec. 5.1, Ex. 4): with M given the equation is
  *     M^T dP/dt M = A^T P M + M^T P A + Q + (Riccati / S terms in M^T P M),
  * solved as the standard form with A M^-1 in place of A and C M^-1 in place
- * of C (the library factors M^T once by LU with partial pivoting on the
- * device); B, R, S keep their meaning.  Needs the dense A.
+ * of C (the library factors M^T once by LU on the device, with partial pivoting
+ * up to 192 rows and tournament pivoting beyond); B, R, S keep their meaning.
+ * Needs the dense A.
  *
  * Sparse A (for DME_ACTION_LEJA, the paper's operator-action method):
  * A_rowptr (n + 1 entries, A_rowptr[0] = 0), A_colind and A_val (nnz

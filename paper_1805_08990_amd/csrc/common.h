@@ -324,7 +324,8 @@ void assemble_f64(hipStream_t s, int64_t n, const double* L1, int64_t r, const d
 void finite_check_f64(hipStream_t s, const double* X, int64_t rows, int64_t cols, int64_t ld,
                       int* flag);
 
-// LU with partial pivoting and the Pade solve (lu.hip)
+// LU (partial pivoting up to 192 rows, tournament pivoting beyond) and the Pade
+// solve (lu.hip)
 struct LuWork;
 // Solve P X = Q in place (Q <- P^-1 Q); P (n x n, ld ldp) is destroyed, Q is
 // n x nrhs (ld ldq).  Returns through *info_dev (device int): 0 ok, j+1 if pivot

@@ -8,7 +8,7 @@
 //   1. ||tX||_1 (column sums on the device)  ->  degree m, scaling s
 //   2. Y = tX / 2^s; even powers Y^2, Y^4, Y^6 (FP64 MFMA GEMMs)
 //   3. U (odd part), V (even part) of the [m/m] numerator; denominator V - U
-//   4. (V - U) F = V + U by LU with partial pivoting (lu.hip)
+//   4. (V - U) F = V + U by LU with row exchanges (lu.hip)
 //   5. F <- F^2, s times
 //
 // An exactly symmetric tX (checked entry by entry, in the pass that takes its

@@ -77,7 +77,7 @@ struct Slab {
         p[u] += KC ? (int64_t)kBK : (int64_t)kBK * ld;
       }
     } else {
-const int hi = lane >> 5, w = (lane >> 1) & (kBK - 1);
+      const int hi = lane >> 5, w = (lane >> 1) & (kBK - 1);
       // a lane takes half of double 32 ii + lane / 2, ii = wave + 4 u
       if (KC) {
         if (rows >= B) {
@@ -1074,7 +1074,10 @@ void gemm_sym_f64(hipStream_t s, char tb, int64_t n, int64_t K, double alpha, co
   const int64_t nt = cdiv(n, p.bm), tiles = nt * (nt + 1) / 2;
   // A long K and few tiles more than fill the chip two to a CU: those few would
   // take as long again as a whole round (n = 4096: 16 of 528 tiles, 1.53 ms in
-  // place of 1.05), so they go as quarters, on four times the CUs.
+  // place of 1.05), so they go as quarters, on four times the CUs: up to 128
+  // tiles, whose quarters are one round.  dme_expm with and without, ms: 16 over
+  // 18.2 and 22.0, 49 (n = 4224) 19.0 and 23.7, 118 (n = 4480) 21.9 and 28.4, 68
+  // beyond five rounds (n = 9216) 154 and 160.
   const int64_t slots = 2 * kMinTiles;
   const int64_t few = (p.bm == 128 && p.nsplit == 1 && K >= 1024 && tiles > slots && tiles % slots <= kMinTiles / 2)
                           ? tiles % slots : 0;

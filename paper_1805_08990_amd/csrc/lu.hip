@@ -1,6 +1,8 @@
-// Dense LU with partial pivoting and the multi-right-hand-side solve used for
-// the Pade denominator of the matrix exponential, (V - U) F = V + U, and for
-// the mass matrix.
+// Dense LU with row exchanges and the multi-right-hand-side solve used for the
+// Pade denominator of the matrix exponential, (V - U) F = V + U, and for the mass
+// matrix.  Pivots are chosen a panel at a time by a tournament (communication
+// avoiding LU, Grigori, Demmel and Xiang 2011); in one level that is partial
+// pivoting, in more its bound on the growth of the entries is weaker.
 //
 // Blocked right-looking factorisation, 64 columns a block, applied to the
 // right-hand sides as it goes (they are further columns of the trailing

@@ -486,8 +486,8 @@ size_t Solver::state_bytes(int64_t n, int64_t m, int64_t p, bool has_S, const dm
 // Mass-matrix form (Sec. 5.1, Ex. 4): M^T dP/dt M = A^T P M + M^T P A + Q + ...
 // becomes the standard form with A M^-1 in place of A and C M^-1 in place of C
 // (Q = C^T C -> M^-T Q M^-1); B, R and S are unchanged.  On the device:
-// A^T <- M^-T A^T and C^T <- M^-T C^T by one LU factorisation of M^T with
-// partial pivoting and a solve with the n + p right-hand sides [A^T, C^T].
+// A^T <- M^-T A^T and C^T <- M^-T C^T by one LU factorisation of M^T with row
+// exchanges and a solve with the n + p right-hand sides [A^T, C^T].
 void Solver::apply_mass_matrix(const double* Mh) {
   DME_REQUIRE(ATp == AT.as<double>() && ATp != nullptr, DME_EINTERNAL, "mass matrix without A^T");
   const int64_t nr = n + p;
@@ -705,8 +705,9 @@ void Solver::plan_beside(int64_t k, int64_t* rows_out, int* ns_out) const {
   *ns_out = 0;
   if (r <= 0 || n < kRowBlock || cus <= xccs) return;
   const bool mixed = opts.precision == DME_MIXED;
-  // Measured on gfx950 (n = 16384, k ~ 178): the tridiagonal reduction takes
-  // about 1.9 us a step; the whole product one wave of workgroups, the FP64
+  // Measured on gfx950 (n = 16384, k ~ 178): beside the rows the tridiagonal
+  // reduction takes about 1.9 us a step (1.8 in FP64, where it takes 1.5 alone,
+  // and 1.9 in the kept form); the whole product one wave of workgroups, the FP64
   // kernel at ~50 TFLOP/s and the split-BF16 kernel reading the FP32
   // operator at ~2.8 TB/s; beside the reduction the FP64 kernel's workgroups
   // run ~1.6x slower than in a whole product (the split-BF16 ones at full
