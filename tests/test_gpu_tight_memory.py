@@ -1,8 +1,8 @@
 """A solve with a dense nonsymmetric operator on a device that has no room for
-several exponentials at a time forms them one after the other, as its error
-messages' last resort, to the same bits.  The device's room is set from the host:
-a small library that stands before the HIP runtime in symbol lookup refuses
-allocations past a limit (in a process of its own)."""
+several exponentials at a time forms them one after the other, to the same bits.
+The device's room is set from the host: a small library that stands before the
+HIP runtime in symbol lookup refuses allocations past a limit (in a process of
+its own)."""
 import os
 import subprocess
 import sys
